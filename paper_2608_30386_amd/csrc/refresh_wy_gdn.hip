@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256) void gdn_factor_kernel(
       x[e] = s <= t ? -(sM[t * SA + s] * sB[s]) : 0.f;
     }
     bf16x8 hi, lo;
-    split8(x, hi, lo);
+    split8_dot(x, hi, lo);
     out[(2 * mu) * 64 + lane] = __builtin_bit_cast(uint4, hi);
     out[(2 * mu + 1) * 64 + lane] = __builtin_bit_cast(uint4, lo);
   }
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(256, 2) void refresh_wy_gdn_kernel(
       float x[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = S[2 * kk + (e >> 2)][e & 3];
-      split8(x, s_hi[kk], s_lo[kk]);
+      split8_dot(x, s_hi[kk], s_lo[kk]);
     }
   };
 
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(256, 2) void refresh_wy_gdn_kernel(
         for (int i = 0; i < 4; ++i)
           x[4 * mu + i] = dot2(as_bf2(vw4[2 * mu + (i >> 1)]), (i & 1) ? kNegHi : kNegLo, X[mu][i]);
       }
-      split8(x, yh, yl);
+      split8_dot(x, yh, yl);
 #pragma unroll
       for (int mu = 0; mu < 2; ++mu) {
         const bf16x8 ah = __builtin_bit_cast(bf16x8, tpr[2 * mu]);
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(256, 2) void refresh_wy_gdn_kernel(
         float xu[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) xu[e] = U[e >> 2][e & 3];
-        split8(xu, uh, ul);
+        split8_dot(xu, uh, ul);
       }
       const float gam = bEG(b)[C - 1];
       const __bf16* sKT = reinterpret_cast<const __bf16*>(bKT(b));

@@ -11,6 +11,7 @@ namespace dasc_wy {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
@@ -30,39 +31,8 @@ __device__ inline __amdgpu_buffer_rsrc_t rsrc(const void* p, int bytes) {
 __device__ inline float ldf(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
 }
-__device__ inline f32x2 ldf2(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
-  return __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
-}
-
 __device__ inline f32x4 ldf4(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
   return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
-}
-
-// The value of the lane N places below (DPP row_shr:N) or above (row_shl:N) this one
-// within its row of 16 lanes; 0 where that lane is outside the row.
-template <int N>
-__device__ inline float row_shr(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
-                                                               0x110 + N, 0xF, 0xF, true));
-}
-template <int N>
-__device__ inline float row_shl(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
-                                                               0x100 + N, 0xF, 0xF, true));
-}
-
-// (m & a) | (~m & b) on the bits: with m all ones or all zeros per lane, a select that
-// stays a single v_bfi_b32 on every lane.
-__device__ inline float bsel(uint32_t m, float a, float b) {
-  return __uint_as_float((__float_as_uint(a) & m) | (__float_as_uint(b) & ~m));
-}
-
-// DPP quad permute: lane k of each group of four takes the value of lane (CTRL >> 2k) & 3
-// of its group (0x55 L broadcasts lane L; 0x90 = [0,0,1,2] shifts up by one lane).
-template <int CTRL>
-__device__ inline float quad_perm(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
-                                                               CTRL, 0xF, 0xF, false));
 }
 
 // p.x * m.x + p.y * m.y + c on the packed-bf16 dot product (v_dot2c_f32_bf16).  With m
@@ -81,15 +51,34 @@ __device__ inline bf16x2 as_bf2(uint32_t w) { return __builtin_bit_cast(bf16x2, 
 constexpr bf16x2 kNegLo = {(__bf16)-1.0f, (__bf16)-0.0f};
 constexpr bf16x2 kNegHi = {(__bf16)0.0f, (__bf16)-1.0f};
 
-__device__ inline void split(float x, __bf16& hi, __bf16& lo) {
-  hi = static_cast<__bf16>(x);
-  lo = static_cast<__bf16>(x - static_cast<float>(hi));
+// Two values split at once into packed bf16 words: hi = (bf16(x0), bf16(x1)) by one packed
+// conversion, lo = the remainders (x - hi, exact in fp32) rounded to bf16.  The remainders
+// take a shift or mask and a subtraction each.  A packed dot product with a unit selector
+// would form a remainder in one instruction, but v_dot2_f32_bf16 shares the matrix pipe: next
+// to a wave that issues MFMAs it takes 9-13 cycles against 4 for a plain VALU instruction
+// (16 values split next to 32x32x16 MFMAs: 235 cycles this way, 339 with dot products; both
+// 224 alone).
+__device__ inline void split2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
+  hi = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x0, x1}, bf16x2));
+  const float r0 = x0 - __uint_as_float(hi << 16), r1 = x1 - __uint_as_float(hi & 0xFFFF0000u);
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{r0, r1}, bf16x2));
 }
 
-// Eight values split at once: hi = bf16(x) two values per packed conversion, and the
-// remainder x - hi (exact in fp32) by one dot2 per value: 2 VALU per value when x dies
-// here, 3 when x lives on (the accumulating dot then needs a copy of it first).
+// Eight values split at once, two per packed word.
 __device__ inline void split8(const float* x, bf16x8& hi, bf16x8& lo) {
+  uint4 h, l;
+  split2(x[0], x[1], h.x, l.x);
+  split2(x[2], x[3], h.y, l.y);
+  split2(x[4], x[5], h.z, l.z);
+  split2(x[6], x[7], h.w, l.w);
+  hi = __builtin_bit_cast(bf16x8, h);
+  lo = __builtin_bit_cast(bf16x8, l);
+}
+
+// The same with the remainders by dot2: 2 VALU per value instead of 3.  For the GDN recurrence,
+// whose waves have their SIMD's matrix pipe nearly to themselves (its fused Load at 8 requests:
+// 80.3 us against 82.6 with split8).
+__device__ inline void split8_dot(const float* x, bf16x8& hi, bf16x8& lo) {
   uint32_t h[4], l[4];
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
@@ -100,15 +89,6 @@ __device__ inline void split8(const float* x, bf16x8& hi, bf16x8& lo) {
   }
   hi = __builtin_bit_cast(bf16x8, make_uint4(h[0], h[1], h[2], h[3]));
   lo = __builtin_bit_cast(bf16x8, make_uint4(l[0], l[1], l[2], l[3]));
-}
-
-// Two values split at once into packed bf16 words: hi = (bf16(x0), bf16(x1)), lo = the
-// remainders (x - hi, exact in fp32) rounded to bf16, as in split8.
-__device__ inline void split2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
-  const bf16x2 hw = __builtin_convertvector(f32x2{x0, x1}, bf16x2);
-  const float r0 = dot2(hw, kNegLo, x0), r1 = dot2(hw, kNegHi, x1);
-  hi = __builtin_bit_cast(uint32_t, hw);
-  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{r0, r1}, bf16x2));
 }
 
 __device__ inline f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) {
@@ -122,6 +102,19 @@ __device__ inline f32x4 mma3(bf16x8 ah, bf16x8 al, bf16x8 bh, bf16x8 bl, f32x4 c
   return mma(ah, bh, c);
 }
 
+// The 32x32x16 form: lane l holds A[l % 32][8 (l / 32) + e], B[8 (l / 32) + e][l % 32] and
+// D[(i % 4) + 8 (i / 4) + 4 (l / 32)][l % 32].  The same rate on the matrix pipe as 16x16x32
+// (32 cycles for twice the work), but it keeps other instructions of the SIMD from issuing for
+// about 10 of its 32 cycles, where two 16x16x32 keep them for about 16.
+__device__ inline f32x16 mmb(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+__device__ inline f32x16 mmb3(bf16x8 ah, bf16x8 al, bf16x8 bh, bf16x8 bl, f32x16 c) {
+  c = mmb(al, bh, c);
+  c = mmb(ah, bl, c);
+  return mmb(ah, bh, c);
+}
+
 // 16x16x16 bf16 MFMA on packed words: lane (q, r) holds A[r][4q .. 4q + 3] and
 // B[4q .. 4q + 3][r], two bf16 per word
 __device__ inline f32x4 mma16(uint2 a, uint2 b, f32x4 c) {
@@ -132,10 +125,6 @@ __device__ inline f32x4 mma16(uint2 a, uint2 b, f32x4 c) {
 
 __device__ inline f32x4 mma32(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-__device__ inline bf16x8 cat(bf16x4 a, bf16x4 b) {
-  return bf16x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
 }
 
 // Operand layout of the register-chained contractions.  One contraction step feeds lane

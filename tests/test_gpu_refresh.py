@@ -256,6 +256,31 @@ def test_kda_fast_and_strong_chunks_interleaved(strong_chunks):
         announce(f"strong chunks {strong_chunks} init={init} max rel err {err:.2e}")
 
 
+@pytest.mark.parametrize("W,strong", [
+    (32, ()), (64, (1,)), (65, (0, 2)), (96, (0,)), (127, (1, 3)), (161, (0, 1, 5)),
+])
+def test_kda_chunk_counts_and_strong_channel_groups(W, strong):
+    # 1 to 6 chunks (the block works on three chunks at a time, so the first and last ones
+    # run with part of its waves idle), and the strong-decay path taken by some groups of 32
+    # channels and not by others: one channel of the second and one of the last group decay
+    # by 2^-461 over each chosen chunk
+    L, H, Hqk, n_req = 1, 3, 3, 2
+    sh = D.Shape("kda", L, H, Hqk, 128, 128)
+    rng = np.random.default_rng(W)
+    g_static = D.dasc_static_log_decay(rng.uniform(math.log(1e-4), 0, size=(L, H, 128)))
+    inv = D.dasc_plan(sh, g_static, "threshold", 0, 64)["inv_row"]
+    pool = (0.05 * rng.standard_normal((3, L, H, 128, 128))).astype(np.float32)
+    pool.reshape(3, -1, 128)[:, inv < 0] = 0.0
+    inp = _inputs_128("kda", n_req, H, Hqk, W, seed=W + 1)
+    for c in strong:
+        inp["g"][:, :, 32 * c:32 * (c + 1), [40, 127]] = -12.0
+    for init in ("restored", "zero"):
+        got = run_refresh(sh, pool, 0, inv, inp, W, init, slots=[2, 0])
+        pairs = [(n, h) for n in range(n_req) for h in range(H)]
+        err = check(sh, pool, got, 0, inv, inp, pairs, init, slots=[2, 0])
+        announce(f"kda W={W} strong={strong} init={init} max rel err {err:.2e}")
+
+
 @pytest.mark.parametrize("kernel", [None, "channel_wy"])
 def test_gdn_fast_and_strong_chunks_interleaved(kernel):
     # The same switch with one gate per token (GDN heads): the chosen chunks decay at every
