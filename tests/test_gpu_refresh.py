@@ -183,6 +183,42 @@ def test_ragged_shapes(arch, dk, dv, H, Hqk, W):
         check(sh, pool, got, 1, inv, inp, pairs, init, slots=slots)
 
 
+@pytest.mark.parametrize("arch,dk,dv,H,Hqk,W", [
+    ("kda", 16, 4, 2, 2, 32), ("gdn", 16, 256, 2, 1, 33),       # one block of columns, all and one
+    ("kda", 32, 64, 2, 2, 31), ("gdn", 32, 68, 4, 4, 64),       # 64 columns a block: exact, one over
+    ("kda", 64, 36, 2, 2, 16), ("kda", 64, 32, 1, 1, 17),       # 32 a block; tiles of 16 tokens
+    ("kda", 128, 16, 2, 2, 15), ("gdn", 128, 52, 2, 2, 48),     # 16 a block
+])
+def test_per_column_kernel_edges(arch, dk, dv, H, Hqk, W):
+    # The per-column kernel at the edges of its column blocks (2048 / dk columns) and token
+    # tiles (32 tokens up to dk = 32, else 16).  Everything is fp32, so a bound on rounding holds
+    # here: about dk + 4 roundings per token of values of the size of the state, summed over
+    # W tokens at worst linearly.
+    L, n_req = 2, 3
+    sh = D.Shape(arch, L, H, Hqk, dk, dv)
+    rng = np.random.default_rng(dk + 7 * dv + W)
+    unit_shape = (L, H, dk) if arch == "kda" else (L, H)
+    g_static = D.dasc_static_log_decay(rng.uniform(math.log(1e-4), 0, size=unit_shape))
+    g_static[1, 0] = math.log(1e-3) / 2.0
+    inv = D.dasc_plan(sh, g_static, "threshold", 0, 64)["inv_row"]
+    pool = (0.05 * rng.standard_normal((4, L, H, dk, dv))).astype(np.float32)
+    k = rng.standard_normal((n_req, Hqk, W, dk)).astype(np.float32)
+    k /= np.linalg.norm(k, axis=-1, keepdims=True)
+    gshape = (n_req, H, W, dk) if arch == "kda" else (n_req, H, W)
+    inp = {
+        "k": bf16_bits_from_f32(k),
+        "v": bf16_bits_from_f32(rng.standard_normal((n_req, H, W, dv)).astype(np.float32)),
+        "g": (-0.3 * np.logaddexp(0, rng.standard_normal(gshape))).astype(np.float32),
+        "beta": (1 / (1 + np.exp(-rng.standard_normal((n_req, H, W))))).astype(np.float32),
+    }
+    slots = [3, 0, 2]
+    for init in ("restored", "zero"):
+        got = run_refresh(sh, pool, 1, inv, inp, W, init, slots=slots)
+        pairs = [(n, h) for n in range(n_req) for h in range(H)]
+        err = check(sh, pool, got, 1, inv, inp, pairs, init, slots=slots)
+        assert err <= W * (dk + 4) * 2.0 ** -24, err
+
+
 def _inputs_128(arch, n_req, H, Hqk, W, seed, g_lo=None):
     rng = np.random.default_rng(seed)
     dk = dv = 128
