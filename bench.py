@@ -90,7 +90,7 @@ def kernel_source_hash() -> str:
     h = hashlib.sha256()
     for f in ("pack_restore.hip", "quant.hip", "refresh.hip", "refresh_wy.hip", "refresh_wy_gdn.hip",
               "refresh_noalloc.hip", "ckpt_layout.h", "refresh_kernels.h", "launch_common.h",
-              "wy_ops.h"):
+              "wy_ops.h", "wy_roles.h"):
         with open(os.path.join(ROOT, "paper_2608_30386_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     with open(os.path.join(ROOT, "paper_2608_30386_amd", "build.py"), "rb") as fh:

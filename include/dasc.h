@@ -25,8 +25,7 @@
  *   - Every argument the host can see is validated before any launch; a failed
  *     check returns an error and launches nothing.
  *   - The caller owns all memory.  The library allocates no device memory and
- *     keeps no state between calls, except the static device scratch array of
- *     dasc_refresh_noalloc (see there).
+ *     keeps no state between calls.
  *   - Device calls are asynchronous on the given stream and never synchronise.
  *     A NULL stream means the default (null) stream.
  *   - Indices that live in device memory (slot lists, row maps) cannot be seen
@@ -58,7 +57,7 @@ extern "C" {
  * earlier error of the caller's matters.  Errors that happen while a kernel runs surface
  * at the caller's next synchronisation, as for any asynchronous launch. */
 #define DASC_E_UNSUPPORTED -5  /* valid request with no kernel built for it      */
-#define DASC_E_SCRATCH     -6  /* needs more than the static scratch of dasc_refresh_noalloc */
+#define DASC_E_SCRATCH     -6  /* larger than dasc_refresh_noalloc takes */
 
 /* Longest replay window dasc_refresh accepts (tokens): keeps every per-head input
  * stream of a dk = 128 head within 1 GiB. */
@@ -281,12 +280,10 @@ int dasc_restore_q8(const dasc_shape *shape, const int8_t *q, const float *scale
 
 /* ---- Load with refresh: bounded-suffix replay (Sec. 4.2 DASC-WR, Eq. 1) --- */
 
-/* Device workspace dasc_refresh and dasc_restore_refresh need for n_req requests and
- * window W.  GDN heads at dk = dv = 128 hold the state-independent factor of every
- * 32-token chunk there (the chunk's (I + A)^{-1} Diag(beta) of the WY form of Eq. 1,
- * split into two bf16 words per entry) between the two launches of their kernel:
- * n_req * n_heads * ceil(W / 32) * 4096 bytes.  Every other shape needs 0.  The caller
- * owns it; its contents need not be initialised and are dead after the call.
+/* Device workspace dasc_refresh and dasc_restore_refresh take for n_req requests and
+ * window W: n_req * n_heads * ceil(W / 32) * 4096 bytes for GDN heads at dk = dv = 128, 0 for
+ * every other shape.  The size is part of the interface: a smaller workspace is refused.  The
+ * kernels keep every chunk's factors on chip and leave the buffer untouched.
  * Errors: DASC_E_INVAL (NULL shape/bytes, n_req < 1, W < 1), DASC_E_SHAPE. */
 int dasc_refresh_workspace_bytes(const dasc_shape *shape, int32_t n_req, int32_t W,
                                  size_t *bytes);
@@ -330,26 +327,19 @@ int dasc_refresh(const dasc_shape *shape, int32_t layer, const int32_t *inv_row,
 
 /* ---- Load with refresh, allocating nothing -------------------------------- */
 
-/* Size of the device scratch array dasc_refresh_noalloc uses in place of a workspace
- * (64 MiB per device: the GDN factor records of, for example, 16 requests x 32 heads at
- * W = 1024, or 8 requests x 32 heads at W = 2048). */
+/* Largest workspace (dasc_refresh_workspace_bytes) of a request dasc_refresh_noalloc takes:
+ * 64 MiB, for example 16 requests x 32 GDN heads at W = 1024, or 8 requests x 32 heads at
+ * W = 2048. */
 #define DASC_NOALLOC_SCRATCH_BYTES (64ll << 20)
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight
- * serving loops, harnesses that forbid hipMalloc): dasc_refresh with no workspace
- * argument.  The scratch dasc_refresh would take from the workspace (the GDN factor
- * records, dasc_refresh_workspace_bytes of them) lives in a device array inside the
- * library, DASC_NOALLOC_SCRATCH_BYTES on each device it runs on, held until the process
- * ends; its device address is looked up once per device, on the first call with that
- * device current.  The call allocates nothing (no hipMalloc, no allocating library
- * routine).  Arguments, layouts, results and precision are those of dasc_refresh; the
- * kernels are the same, so the results are bit-identical to dasc_refresh's.
- * Every call on one device shares that device's array: calls that overlap on one device
- * (different streams, or threads without ordering) race and must not be issued.  The
- * stream must belong to the current device.
+ * serving loops, harnesses that forbid hipMalloc): dasc_refresh with no workspace argument.
+ * The call allocates nothing (no hipMalloc, no allocating library routine).  Arguments,
+ * layouts, results and precision are those of dasc_refresh; the kernels are the same, so the
+ * results are bit-identical to dasc_refresh's.
  * Errors: those of dasc_refresh (without DASC_E_WORKSPACE); DASC_E_SCRATCH, before
  * anything is launched, when dasc_refresh_workspace_bytes for this shape, n_req and W
- * exceeds DASC_NOALLOC_SCRATCH_BYTES; DASC_E_HIP if the array's address cannot be found. */
+ * exceeds DASC_NOALLOC_SCRATCH_BYTES. */
 int dasc_refresh_noalloc(const dasc_shape *shape, int32_t layer, const int32_t *inv_row,
                          float *states, int64_t n_pool, const int32_t *slot,
                          const uint16_t *k, const uint16_t *v, const float *g, const float *beta,
@@ -358,8 +348,7 @@ int dasc_refresh_noalloc(const dasc_shape *shape, int32_t layer, const int32_t *
 /* ---- Load with refresh, fused (Sec. 4.2: restore, then DASC-WR) ----------- */
 
 /* What dasc_restore followed by dasc_refresh does for one layer, without the separate
- * restore pass (one launch for KDA heads; GDN heads take two, the state-independent
- * factor launch of dasc_refresh and then the fused recurrence):
+ * restore pass, in one launch:
  * for each request i < n_req, the rows of layer `layer` of states[dst_slot[i]] receive
  *   - omitted rows of heads that have any (KDA rows; GDN whole heads): S'_W of the
  *     replay above, started from the restored head (kept rows taken from checkpoint

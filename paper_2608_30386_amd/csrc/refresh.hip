@@ -250,9 +250,18 @@ void launch_column(bool per_channel, int64_t heads, hipStream_t st, int H, int H
   }
 }
 
-// Does this shape take the two-launch scalar-gate GDN kernel?
-bool uses_gdn_factors(const dasc_shape* shape) {
+// Does this shape take the scalar-gate GDN kernel?
+bool uses_gdn_kernel(const dasc_shape* shape) {
   return shape->arch == DASC_ARCH_GDN && dasc::refresh_wy_supported(shape->dk, shape->dv);
+}
+
+// The workspace the interface reserves for the GDN kernel: 4 KiB per 32-token chunk and head.
+size_t gdn_workspace_bytes(int n_req, int H, int W) {
+  return size_t(n_req) * size_t(H) * size_t((int64_t(W) + 31) / 32) * size_t(4096);
+}
+// Largest request list the GDN path takes: heads times groups of four chunks within 32 bits.
+bool gdn_size_ok(int n_req, int H, int W) {
+  return int64_t(n_req) * H * (((int64_t(W) + 31) / 32 + 3) / 4) <= INT32_MAX;
 }
 
 }  // namespace
@@ -261,11 +270,7 @@ extern "C" int dasc_refresh_workspace_bytes(const dasc_shape* shape, int32_t n_r
                                             size_t* bytes) {
   if (!shape || !bytes || n_req < 1 || W < 1) return DASC_E_INVAL;
   if (!dasc::valid_shape(shape)) return DASC_E_SHAPE;
-  // GDN heads at dk = dv = 128 keep each chunk's WY factor -T' between the two launches
-  // of their kernel; every other path needs nothing.
-  *bytes = uses_gdn_factors(shape)
-               ? dasc::gdn_factor_workspace_bytes(n_req, shape->n_heads, W)
-               : 0;
+  *bytes = uses_gdn_kernel(shape) ? gdn_workspace_bytes(n_req, shape->n_heads, W) : 0;
   return DASC_OK;
 }
 
@@ -277,7 +282,8 @@ namespace dasc {
 int refresh_impl(const dasc_shape* shape, int32_t layer, const int32_t* inv_row, float* states,
                  int64_t n_pool, const int32_t* slot, const uint16_t* k, const uint16_t* v,
                  const float* g, const float* beta, int32_t n_req, int32_t W, int32_t init_mode,
-                 void* workspace, size_t workspace_bytes, int32_t kernel, dasc_stream_t stream) {
+                 const void* workspace, size_t workspace_bytes, bool noalloc, int32_t kernel,
+                 dasc_stream_t stream) {
   if (!shape) return DASC_E_INVAL;
   if (!dasc::valid_shape(shape) || shape->dv % 4 != 0) return DASC_E_SHAPE;
   if (layer < 0 || layer >= shape->n_layers || n_req < 1 || W < 1 || W > DASC_MAX_WINDOW ||
@@ -293,22 +299,21 @@ int refresh_impl(const dasc_shape* shape, int32_t layer, const int32_t* inv_row,
   if (dv > 256) return DASC_E_UNSUPPORTED;
   if (kernel == DASC_REFRESH_KERNEL_CHANNEL_WY && !dasc::refresh_wy_supported(dk, dv))
     return DASC_E_UNSUPPORTED;
-  const bool gdn_factors = kernel == DASC_REFRESH_KERNEL_AUTO && uses_gdn_factors(shape);
-  const size_t need =
-      gdn_factors ? dasc::gdn_factor_workspace_bytes(n_req, shape->n_heads, W) : 0;
+  const bool gdn_kernel = kernel == DASC_REFRESH_KERNEL_AUTO && uses_gdn_kernel(shape);
+  const size_t need = gdn_kernel && !noalloc ? gdn_workspace_bytes(n_req, shape->n_heads, W) : 0;
   if (workspace_bytes < need || (need > 0 && !workspace)) return DASC_E_WORKSPACE;
   if (need > 0 && !dasc::aligned16(workspace)) return DASC_E_INVAL;
-  if (2 * int64_t(n_req) * shape->n_heads > INT32_MAX) return DASC_E_INVAL;  // GDN: 2 blocks a head
+  if (2 * int64_t(n_req) * shape->n_heads > INT32_MAX) return DASC_E_INVAL;
 
   const bool per_channel = shape->arch == DASC_ARCH_KDA;
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   const int zero = init_mode == DASC_INIT_ZERO;
   (void)hipGetLastError();
-  if (gdn_factors) {
-    if (dasc::gdn_factor_blocks(n_req, shape->n_heads, W) > INT32_MAX) return DASC_E_INVAL;
+  if (gdn_kernel) {
+    if (!gdn_size_ok(n_req, shape->n_heads, W)) return DASC_E_INVAL;
     dasc::launch_refresh_wy_gdn(n_req, shape->n_heads, shape->n_qk_heads, layer,
                                 shape->n_layers, inv_row, states, n_pool, slot, k, v, g, beta, W,
-                                zero, workspace, st);
+                                zero, st);
     return dasc::launch_status();
   }
   if (kernel != DASC_REFRESH_KERNEL_COLUMN && dasc::refresh_wy_supported(dk, dv)) {
@@ -339,7 +344,7 @@ extern "C" int dasc_refresh(const dasc_shape* shape, int32_t layer, const int32_
                             const float* beta, int32_t n_req, int32_t W, int32_t init_mode,
                             void* workspace, size_t workspace_bytes, dasc_stream_t stream) {
   return dasc::refresh_impl(shape, layer, inv_row, states, n_pool, slot, k, v, g, beta, n_req, W,
-                            init_mode, workspace, workspace_bytes, DASC_REFRESH_KERNEL_AUTO,
+                            init_mode, workspace, workspace_bytes, false, DASC_REFRESH_KERNEL_AUTO,
                             stream);
 }
 
@@ -350,7 +355,7 @@ extern "C" int dasc_refresh_select(const dasc_shape* shape, int32_t layer, const
                                    void* workspace, size_t workspace_bytes, int32_t kernel,
                                    dasc_stream_t stream) {
   return dasc::refresh_impl(shape, layer, inv_row, states, n_pool, slot, k, v, g, beta, n_req, W,
-                            init_mode, workspace, workspace_bytes, kernel, stream);
+                            init_mode, workspace, workspace_bytes, false, kernel, stream);
 }
 
 extern "C" int dasc_restore_refresh(const dasc_shape* shape, int32_t layer, const float* ckpt,
@@ -383,16 +388,16 @@ extern "C" int dasc_restore_refresh(const dasc_shape* shape, int32_t layer, cons
   if (workspace_bytes < need || (need > 0 && !workspace)) return DASC_E_WORKSPACE;
   if (need > 0 && !dasc::aligned16(workspace)) return DASC_E_INVAL;
   if (!dasc::refresh_wy_supported(shape->dk, shape->dv)) return DASC_E_UNSUPPORTED;
-  if (2 * int64_t(n_req) * shape->n_heads > INT32_MAX) return DASC_E_INVAL;  // GDN: 2 blocks a head
+  if (2 * int64_t(n_req) * shape->n_heads > INT32_MAX) return DASC_E_INVAL;
   if (n_rows == 0) slice_rows = 1;  // nothing is read; keeps the divisor non-zero
   (void)hipGetLastError();
   // GDN heads take the scalar-gate kernel, as in dasc_refresh
-  if (uses_gdn_factors(shape)) {
-    if (dasc::gdn_factor_blocks(n_req, shape->n_heads, W) > INT32_MAX) return DASC_E_INVAL;
+  if (uses_gdn_kernel(shape)) {
+    if (!gdn_size_ok(n_req, shape->n_heads, W)) return DASC_E_INVAL;
     dasc::launch_restore_refresh_wy_gdn(n_req, shape->n_heads, shape->n_qk_heads, layer,
                                         shape->n_layers, ckpt, n_ckpt_slots, src_slot, slice_rows,
                                         n_rows, inv_row, states, n_pool, dst_slot, k, v, g, beta,
-                                        W, init_mode == DASC_INIT_ZERO, workspace,
+                                        W, init_mode == DASC_INIT_ZERO,
                                         reinterpret_cast<hipStream_t>(stream));
   } else
     dasc::launch_restore_refresh_wy(shape->arch == DASC_ARCH_KDA, n_req, shape->n_heads,

@@ -73,20 +73,21 @@
 #include "ckpt_layout.h"
 #include "refresh_kernels.h"
 #include "wy_ops.h"
+#include "wy_roles.h"
 
 namespace {
 
 using namespace dasc_wy;
 
 constexpr int C = 32;       // tokens per chunk
-constexpr int D = 128;      // dk = dv
+constexpr int D = kDim;     // dk = dv
 constexpr float kGateFloor = -10.f;
 // Fast path bound: every channel's log2-decay over a chunk at least -kFastRange, so that
 // k 2^G and k 2^{-G} stay normal fp32 (and their bf16 low parts too) for every token.
 constexpr float kFastRange = 96.f;
 constexpr float kLog2e = 1.4426950408889634f;
 
-constexpr int kStateWaves = 4;    // waves 0..3
+constexpr int kStateWaves = 4;    // waves 0..3, 32 value columns each
 constexpr int kFactorWaves = 4;   // waves 4..7
 constexpr int kWaves = kStateWaves + kFactorWaves + 1;   // wave 8 solves
 constexpr int kThreads = 64 * kWaves;
@@ -96,15 +97,13 @@ constexpr int KG_BYTES = 8 * 2 * 1024;           // [step of 16 channels][hi/lo]
 constexpr int KH_HALF = 32 * 16 + 16;            // 32 channels x 8 bf16, padded
 constexpr int KH_BYTES = 4 * 2 * 2 * 2 * KH_HALF;   // [32 channels][hi/lo][step][lane / 32][KH_HALF]
 constexpr int AP_BYTES = 3 * 4 * 1024;           // [tile][factor wave][lane][4 f32]
-constexpr int TP_BYTES = 2 * 2 * 1024;           // [step of 16 tokens][hi/lo][lane][8 bf16]
 constexpr int OFF_KG = 0;                        // 3 buffers
 constexpr int OFF_KH = OFF_KG + 3 * KG_BYTES;    // 2 buffers
 constexpr int OFF_AP = OFF_KH + 2 * KH_BYTES;    // 2 buffers
 constexpr int OFF_TP = OFF_AP + 2 * AP_BYTES;    // 2 buffers
-constexpr int OFF_GAM = OFF_TP + 2 * TP_BYTES;   // f32 [3][D] 2^{G_C}
-constexpr int ST = 20;                           // row stride (f32) of the solver's blocks
-constexpr int OFF_TR = OFF_GAM + 3 * D * 4;      // f32 [2][32][ST] A, then T
-constexpr int OFF_BETA = OFF_TR + 2 * 32 * ST * 4;   // f32 [64] the solver's betas (twice)
+constexpr int OFF_GAM = OFF_TP + 2 * TP32_BYTES;   // f32 [3][D] 2^{G_C}
+constexpr int OFF_TR = OFF_GAM + 3 * D * 4;      // the solver's A, then T
+constexpr int OFF_BETA = OFF_TR + 2 * T_BYTES;   // f32 [64] the solver's betas (twice)
 constexpr int OFF_ROWS = OFF_BETA + 64 * 4;      // int64 [D] fused: checkpoint row table
 constexpr int OFF_OMIT = OFF_ROWS + D * 8;       // u8 [D] row omitted (replayed)
 constexpr int LDS_BYTES = OFF_OMIT + D;
@@ -113,33 +112,9 @@ static_assert(LDS_BYTES <= 160 * 1024, "one block per CU");
 // Packed checkpoint of the fused variant (unused when FUSED is false).
 using dasc::CkptView;
 
-// One DPP read: lane l takes v from the lane CTRL selects within its row of 16 (0 where that
-// lane is outside the row).
-template <int CTRL>
-__device__ inline float dpp_row(float v) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
-                                                               0xF, 0xF, true));
-}
 // Lane L of the row of 16 to every lane of the row (row_newbcast).
 template <int L>
 __device__ inline float row_bcast(float v) { return dpp_row<0x150 + L>(v); }
-
-// A 16x16 block in the accumulator layout (lane (q, r) holds rows 4q + i of column r), split
-// hi/lo into two packed words: the 16x16x16 bf16 MFMA's operand layout for the left factor's
-// transpose and for the right factor.
-struct Split4 { uint2 h, l; };
-__device__ inline Split4 split4(const f32x4 x) {
-  Split4 s;
-  split2(x[0], x[1], s.h.x, s.l.x);
-  split2(x[2], x[3], s.h.y, s.l.y);
-  return s;
-}
-// left * right + c, the left factor given transposed
-__device__ inline f32x4 mulb(const Split4& lt, const Split4& rt, f32x4 c) {
-  c = mma16(lt.l, rt.h, c);
-  c = mma16(lt.h, rt.l, c);
-  return mma16(lt.h, rt.h, c);
-}
 
 template <bool PER_CHANNEL, bool FUSED>
 __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
@@ -173,9 +148,8 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
 
   const bool factor_wave = w >= kStateWaves && w < kStateWaves + kFactorWaves;
   // Fused: where dense row c of this head sits in the checkpoint, as a float offset
-  // (kOmitted for an omitted row, kNoRow for an index outside the packed rows, which
-  // restores as +0.0).
-  using dasc::kOmitted;
+  // (dasc::kOmitted for an omitted row, dasc::kNoRow for an index outside the packed rows,
+  // which restores as +0.0).
   int64_t* sOff = reinterpret_cast<int64_t*>(smem + OFF_ROWS);
   if (tid < D) {
     sOmit[tid] = inv < 0;
@@ -187,13 +161,7 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
   if (FUSED && (cslot < 0 || cslot >= ck.n_slots)) return;
   float* S_head = states + (sl * L * H * D + head_row) * D;
   if (FUSED && !any_omitted) {   // nothing to replay: a plain copy of the head
-    for (int e = tid; e < D * D / 4; e += kThreads) {
-      const int c = e >> 5, v4 = e & 31;
-      const int64_t o = sOff[c];
-      const f32x4 val = o >= 0 ? reinterpret_cast<const f32x4*>(ck.ckpt + o)[v4]
-                               : f32x4{0.f, 0.f, 0.f, 0.f};
-      reinterpret_cast<f32x4*>(S_head + int64_t(c) * D)[v4] = val;
-    }
+    copy_head(S_head, ck.ckpt, sOff, tid, kThreads);
     return;
   }
 
@@ -344,12 +312,7 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
     // ---- solver wave ------------------------------------------------------------------------
     const __amdgpu_buffer_rsrc_t rb = rsrc(bp, W * 4);
     float* const sB = reinterpret_cast<float*>(smem + OFF_BETA);
-    // rows 0..15 of the second token step of -T' are zero
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int hl = 0; hl < 2; ++hl)
-        if ((lane & 16) == 0)
-          *reinterpret_cast<uint4*>(smem + OFF_TP + b * TP_BYTES + 2048 + 1024 * hl + lane * 16) = make_uint4(0, 0, 0, 0);
+    for (int b = 0; b < 2; ++b) clear_tp(smem + OFF_TP + b * TP32_BYTES, lane);
     float braw = ldf(rb, (lane & (C - 1)) * 4, 0);
     float* const tr = reinterpret_cast<float*>(smem + OFF_TR);
     for (int p = -2; p < n_chunks; ++p) {
@@ -372,63 +335,7 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
           tr[(16 + 4 * q + i) * ST + r] = acc[2][i] * b1[i];
         }
         wave_lds_sync();
-        // T = (I + A)^{-1} row by row from T (I + A) = I: lane r of diagonal block blk takes row
-        // r, columns descending; once T[r][s] is known it is taken out of the columns before it
-        // (T[r][c] -= T[r][s] A[s][c]), which need row s of A, the same for all lanes of the
-        // block.  Both blocks at once on lanes 0..31 (lanes 32..63 repeat them).
-        const int blk = q & 1;
-        const float* ar = tr + 16 * blk * ST;
-        float y[16];
-#pragma unroll
-        for (int t = 0; t < 16; ++t) y[t] = t == r ? 1.f : 0.f;
-#pragma unroll
-        for (int t = 15; t > 0; --t) {
-#pragma unroll
-          for (int c4 = 0; c4 < (t + 3) / 4; ++c4) {
-            const f32x4 x = *reinterpret_cast<const f32x4*>(ar + t * ST + 4 * c4);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (4 * c4 + i < t) y[4 * c4 + i] = fmaf(-y[t], x[i], y[4 * c4 + i]);
-          }
-        }
-        // the diagonal blocks of -T' = -T Diag(beta), rows by lane: tokens 4 h2 .. + 3 and
-        // 8 + 4 h2 .. + 3 of a row sit together (lanes of the two halves take one h2 each)
-        unsigned char* const tp = smem + OFF_TP + (c & 1) * TP_BYTES;
-        float* const tf = tr + 32 * ST;   // T, rows
-        const int h2 = q >> 1;
-        float o[8];
-        {
-          const f32x4 ba = *reinterpret_cast<const f32x4*>(sB + 16 * blk + 4 * h2);
-          const f32x4 bb = *reinterpret_cast<const f32x4*>(sB + 16 * blk + 8 + 4 * h2);
-          f32x4 ya, yb;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            ya[i] = h2 ? y[4 + i] : y[i];
-            yb[i] = h2 ? y[12 + i] : y[8 + i];
-            o[i] = -(ya[i] * ba[i]);
-            o[4 + i] = -(yb[i] * bb[i]);
-          }
-          *reinterpret_cast<f32x4*>(tf + (16 * blk + r) * ST + 4 * h2) = ya;
-          *reinterpret_cast<f32x4*>(tf + (16 * blk + r) * ST + 8 + 4 * h2) = yb;
-        }
-        bf16x8 oh, ol;
-        split8(o, oh, ol);
-        unsigned char* const od = tp + (2048 + 256) * blk + (r + 32 * h2) * 16;
-        *reinterpret_cast<bf16x8*>(od) = oh;
-        *reinterpret_cast<bf16x8*>(od + 1024) = ol;
-        wave_lds_sync();
-        // T10 = -T11 A10 T00, formed as its transpose -T00^T (A10^T T11^T): lane (q, r) then
-        // holds row r of the block at tokens 4q .. 4q + 3
-        f32x4 t00;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) t00[i] = tf[(4 * q + i) * ST + r];
-        const f32x4 t11t = *reinterpret_cast<const f32x4*>(tf + (16 + r) * ST + 4 * q);
-        const f32x4 z = mulb(split4(a10), split4(t11t), zero4);
-        const f32x4 t10 = mulb(split4(t00), split4(z), zero4) * b0;   // -T10 Diag(beta)
-        const Split4 o10 = split4(t10);
-        unsigned char* const o1 = tp + 256 + (r + 32 * (q & 1)) * 16 + (q >> 1) * 8;
-        *reinterpret_cast<uint2*>(o1) = o10.h;
-        *reinterpret_cast<uint2*>(o1 + 1024) = o10.l;
+        solve_chunk<false>(tr, a10, sB, b0, nullptr, tr + 32 * ST, smem + OFF_TP + (c & 1) * TP32_BYTES, q, r);
       }
       __syncthreads();
     }
@@ -450,43 +357,10 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
   fetch_v(0);
   // S'[c][col] for c = 32 mt + (i % 4) + 8 (i / 4) + 4 hi
   f32x16 S[4] = {};
-  if (!init_zero) {
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      // the addresses of 16 rows, then their loads: a row that restores as +0.0 reads the
-      // head's own pool row instead and drops it, so that no load waits on a branch
-      float val[16];
-      bool ok[16];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int c = 32 * mt + (i & 3) + 8 * (i >> 2) + 4 * hi;
-        const float* src = S_head + int64_t(c) * D;
-        ok[i] = true;
-        if (FUSED) {
-          const int64_t o = sOff[c];
-          ok[i] = o >= 0;
-          src = ok[i] ? ck.ckpt + o : src;
-        }
-        val[i] = src[col];
-      }
-#pragma unroll
-      for (int i = 0; i < 16; ++i) S[mt][i] = ok[i] ? val[i] : 0.f;
-    }
-  }
+  if (!init_zero) load_state<FUSED>(S, S_head, ck.ckpt, sOff, col, hi);
   __syncthreads();
-  if (FUSED) {
-    // Every row that is not replayed is final already: its checkpoint row (or +0.0) is
-    // copied to the pool here, 16 bytes per thread and access, while the first chunk is
-    // being solved.
-#pragma unroll 4
-    for (int e = tid; e < D * D / 4; e += 64 * kStateWaves) {
-      const int c = e >> 5, v4 = e & 31;
-      const int64_t o = sOff[c];
-      const f32x4 val = reinterpret_cast<const f32x4*>(o >= 0 ? ck.ckpt + o : S_head + int64_t(c) * D)[v4];
-      if (o != kOmitted)
-        reinterpret_cast<f32x4*>(S_head + int64_t(c) * D)[v4] = o >= 0 ? val : zero4;
-    }
-  }
+  // (kept rows are written while the first chunk is being solved)
+  if (FUSED) copy_kept_rows<64 * kStateWaves>(S_head, ck.ckpt, sOff, tid);
   __syncthreads();
 
   struct Frag { bf16x8 h, l; };
@@ -506,7 +380,7 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
   Frag gf = load_kg(0, 0), sf = split_s(0);
   int kg_buf = 0;
   for (int c = 0; c < n_chunks; ++c) {
-    const bf16x8* tp = reinterpret_cast<const bf16x8*>(smem + OFF_TP + (c & 1) * TP_BYTES) + lane;
+    const bf16x8* tp = reinterpret_cast<const bf16x8*>(smem + OFF_TP + (c & 1) * TP32_BYTES) + lane;
     const float* gamp = reinterpret_cast<const float*>(smem + OFF_GAM) + kg_buf * D + 4 * hi;
     const unsigned char* kh = smem + OFF_KH + (c & 1) * KH_BYTES + hi * KH_HALF + (lane & 31) * 16;
     auto load_kh = [&](int mt, int s) {
@@ -584,18 +458,7 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
     __syncthreads();
   }
 
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-    for (int gr = 0; gr < 4; ++gr) {
-      // rows 32 mt + 8 gr + 4 hi .. + 3: one omitted flag per byte
-      const uint32_t om = *reinterpret_cast<const uint32_t*>(sOmit + 32 * mt + 8 * gr + 4 * hi);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int c = 32 * mt + 8 * gr + 4 * hi + i;
-        if ((om >> (8 * i)) & 0xFFu) S_head[int64_t(c) * D + col] = S[mt][4 * gr + i];
-      }
-    }
+  store_state(S, S_head, sOmit, col, hi);
 }
 
 }  // namespace

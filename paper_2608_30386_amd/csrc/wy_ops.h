@@ -38,22 +38,6 @@ __device__ inline f32x4 ldf4(__amdgpu_buffer_rsrc_t r, int voff, int soff) {
   return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
 }
 
-// p.x * m.x + p.y * m.y + c on the packed-bf16 dot product (v_dot2c_f32_bf16).  With m
-// a unit selector (+-1 in one half, 0 in the other) it reads one bf16 of a packed word
-// straight into an fp32 sum: one instruction instead of an unpack and an add.  The
-// products are exact, so the result is the fp32 sum c +- p.e rounded once.
-__device__ inline float dot2(bf16x2 p, bf16x2 m, float c) {
-  return __builtin_amdgcn_fdot2_f32_bf16(p, m, c, false);
-}
-__device__ inline bf16x2 as_bf2(uint32_t w) { return __builtin_bit_cast(bf16x2, w); }
-// Selectors -(low half) and -(high half).  The low one carries -0 in its high half: the
-// word (-1, +0) is the fp32 inline constant -1.0's low-half image, which the compiler
-// encodes as that constant while the hardware reads it as the fp32 word (+0, -1).
-// (-1, -0) has no inline encoding, so it goes out as the literal it is; -0 * x adds
-// nothing to the sum.
-constexpr bf16x2 kNegLo = {(__bf16)-1.0f, (__bf16)-0.0f};
-constexpr bf16x2 kNegHi = {(__bf16)0.0f, (__bf16)-1.0f};
-
 // Two values split at once into packed bf16 words: hi = (bf16(x0), bf16(x1)) by one packed
 // conversion, lo = the remainders (x - hi, exact in fp32) rounded to bf16.  The remainders
 // take a shift or mask and a subtraction each.  A packed dot product with a unit selector
@@ -76,22 +60,6 @@ __device__ inline void split8(const float* x, bf16x8& hi, bf16x8& lo) {
   split2(x[6], x[7], h.w, l.w);
   hi = __builtin_bit_cast(bf16x8, h);
   lo = __builtin_bit_cast(bf16x8, l);
-}
-
-// The same with the remainders by dot2: 2 VALU per value instead of 3.  For the GDN recurrence,
-// whose waves have their SIMD's matrix pipe nearly to themselves (its fused Load at 8 requests:
-// 80.3 us against 82.6 with split8).
-__device__ inline void split8_dot(const float* x, bf16x8& hi, bf16x8& lo) {
-  uint32_t h[4], l[4];
-#pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const bf16x2 hw = __builtin_convertvector(f32x2{x[2 * p], x[2 * p + 1]}, bf16x2);
-    const float r0 = dot2(hw, kNegLo, x[2 * p]), r1 = dot2(hw, kNegHi, x[2 * p + 1]);
-    h[p] = __builtin_bit_cast(uint32_t, hw);
-    l[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{r0, r1}, bf16x2));
-  }
-  hi = __builtin_bit_cast(bf16x8, make_uint4(h[0], h[1], h[2], h[3]));
-  lo = __builtin_bit_cast(bf16x8, make_uint4(l[0], l[1], l[2], l[3]));
 }
 
 __device__ inline f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) {
@@ -125,18 +93,5 @@ __device__ inline f32x4 mma16(uint2 a, uint2 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a),
                                                    __builtin_bit_cast(s16x4, b), c, 0, 0, 0);
 }
-
-__device__ inline f32x4 mma32(float a, float b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-// Operand layout of the register-chained contractions.  One contraction step feeds lane
-// (q, r) the index order k(q, e) = 4q + e (e < 4), 16 + 4q + e - 4 (e >= 4) within a group
-// of 32.  Operands staged in LDS along that index are stored interleaved: the four entries
-// at 4q .. 4q + 3 and the four at 16 + 4q .. 16 + 4q + 3 sit side by side at 8q, so that
-// the lane reads its operand in one 16-byte access.  ilv maps a 4-aligned index to its
-// stored position; ld16 reads the eight entries at a stored position.
-__device__ inline int ilv(int x) { return (x & ~31) | ((x & 15) << 1) | ((x & 16) >> 2); }
-__device__ inline bf16x8 ld16(const __bf16* p) { return *reinterpret_cast<const bf16x8*>(p); }
 
 }  // namespace dasc_wy

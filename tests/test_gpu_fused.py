@@ -194,3 +194,37 @@ def test_qwen_gdn_fused_one_layer():
     assert np.array_equal(g_[dst], r_[dst]), "fused differs from restore + refresh"
     announce(f"qwen_gdn fused layer={layer}: all {len(pairs)} heads, max rel err {err:.2e}, "
              "bit-equal to unfused")
+
+
+@pytest.mark.parametrize("n_req", [32, 33])
+def test_gdn_blocks_per_head(n_req):
+    # GDN launches of up to 128 heads take two blocks per head (32 requests x 4 heads), larger
+    # ones one (33 x 4); slow decays, which the kernel carries over several chunks before it
+    # multiplies them into the state, next to fast ones; a ragged last chunk
+    L, H, Hqk, W = 1, 4, 2, 165
+    sh = D.Shape("gdn", L, H, Hqk, 128, 128)
+    rng = np.random.default_rng(n_req)
+    g_static = np.full((L, H), math.log(1e-3) / 2.0)
+    g_static[0, 2] = math.log(1e-3) / 1000.0               # head 2 kept
+    plan = D.dasc_plan(sh, g_static, "threshold", 0, 64)
+    R = int(plan["n_rows"])
+    states = (0.05 * rng.standard_normal((n_req, L, H, 128, 128))).astype(np.float32)
+    inp = _inputs_128("gdn", n_req, H, Hqk, W, seed=n_req)
+    inp["g"] *= np.array([0.02, 0.3, 1.0, 3.0], np.float32)[None, :, None]
+    ck_slots = list(rng.permutation(n_req + 1)[:n_req])
+    dst = list(rng.permutation(n_req + 2)[:n_req])
+    ck = oracle_ckpt(states, plan["unit_row"], n_req + 1, ck_slots, 1, R)
+    restored = oracle_restored(ck, ck_slots, plan["unit_row"], sh.rows, 128, R)
+    pool = sentinel_pool(n_req + 2, sh)
+    pairs = [(n, h) for n in (0, n_req - 1) for h in (0, 1, 3)]
+    got = run_fused(sh, 0, ck, ck_slots, plan["inv_row"], pool, dst, inp, W, R, 1, R)
+    ref = run_unfused(sh, 0, ck, ck_slots, plan["inv_row"], pool, dst, inp, W, R, 1, R)
+    assert np.array_equal(got.view(np.uint32)[dst], ref.view(np.uint32)[dst])
+    layer_in = restored.view(np.float32).reshape(n_req, H, 128, 128)
+    want, om = OR.refresh(layer_in, plan["inv_row"], inp["k"], inp["v"], inp["g"], inp["beta"], Hqk,
+                          pairs=pairs)
+    err = OR.refresh_error(np.stack([got[dst[n], 0, h] for n, h in pairs]), want, om, pairs)
+    assert err <= TOL, err
+    kept = got.reshape(n_req + 2, H, 128, 128)[dst][:, 2].view(np.uint32)
+    assert np.array_equal(kept, restored.reshape(n_req, H, 128, 128)[:, 2])
+    announce(f"gdn n_req={n_req}: fused bit-equal to unfused, max rel err {err:.2e}")
