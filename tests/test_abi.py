@@ -367,3 +367,16 @@ def test_code_independence():
         if f.endswith(".py"):
             text = open(os.path.join(wl, f)).read()
             assert not re.search(r"^\s*(from|import)\s+(oracle|paper_2608_30386_amd)\b", text, re.M)
+
+
+def test_shape_copies_and_pickles_after_use():
+    # a Shape keeps its C struct once a call has used it; copies and pickles carry the fields only
+    import copy
+    import dataclasses
+    import pickle
+
+    a = D.Shape("gdn", 2, 4, 2, 16, 32)
+    assert a.rows == 128 and a._ref is a._ref
+    for b in (copy.copy(a), copy.deepcopy(a), pickle.loads(pickle.dumps(a))):
+        assert b == a and hash(b) == hash(a) and b.rows == 128
+    assert dataclasses.replace(a, dk=32).rows == 256
