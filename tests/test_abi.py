@@ -375,6 +375,8 @@ def test_shape_copies_and_pickles_after_use():
     import dataclasses
     import pickle
 
+    import paper_2608_30386_amd as D
+
     a = D.Shape("gdn", 2, 4, 2, 16, 32)
     assert a.rows == 128 and a._ref is a._ref
     for b in (copy.copy(a), copy.deepcopy(a), pickle.loads(pickle.dumps(a))):
