@@ -23,15 +23,17 @@
 //
 // What bounds it: instruction issue.  A SIMD issues one VALU instruction in 4 cycles (8 for an
 // exponential), a 32x32x16 MFMA holds the others back for about 10 of its 32, and a state
-// wave's ~390 and a factor wave's ~345 VALU instructions a chunk fill 4.5k cycles of their
-// SIMD; SIMD 0 also carries the solver (5.4k).  Hence the 32x32x16 tiles instead of 16x16x32,
+// wave's ~390 and a factor wave's ~345 VALU instructions a chunk (64 and 48 fewer when the
+// decay is not applied, see below) fill 4.5k cycles of their SIMD; SIMD 0 also carries the
+// solver (5.4k).  Hence the 32x32x16 tiles instead of 16x16x32,
 // the split without dot products (wy_ops.h), and every operand staged in the order its reader
 // loads it, 16 bytes per lane.  Waves of the same SIMD are served oldest first unless their
 // priorities differ: the solver, which everything waits for, goes first, then the state waves.
 //
 // Measured (us; before: one 256-thread block per head, two per CU): fused Load of 16 requests x
-// 32 heads, W = 1024: 223.7 -> 211.6; the plain refresh, W = 2048: 430.3 -> 392.4; of 5
-// requests, W = 777: 126.6 -> 68.2; fused Load of 1 request, W = 128: 30.2 -> 19.7.
+// 32 heads, W = 1024: 223.2 -> 205.7; the plain refresh, W = 2048: 426.3 -> 383.8; of 5
+// requests, W = 777: 126.8 -> 67.8; fused Load of 1 request, W = 128: 30.1 -> 19.5.  With all 256
+// CUs busy the clock falls from 2.45 to 2.1 GHz, which is why the batches gain less.
 //
 // Precision.  The products run on bf16 MFMA with fp32 accumulation.  An fp32 operand x is
 // split into x_hi = bf16(x) and x_lo = bf16(x - x_hi); a product is formed as a_lo b_hi +
@@ -48,12 +50,20 @@
 // Decay factors.  exp(G_t - G_s) <= 1 for s <= t, but a factorised form needs
 // exp(G_t - G_ref) exp(G_ref - G_s).  Fast path: when each of a factor wave's 32 channels
 // decays by at most 2^96 over the chunk (a test per wave; realistic gates decay far less), the
-// reference is the chunk start: A = Diag(beta) strictly-lower(K_G Q^T) with K_G = k 2^G (which
+// reference is where G starts: A = Diag(beta) strictly-lower(K_G Q^T) with K_G = k 2^G (which
 // X needs anyway) and Q = k 2^{-G} <= 2^96 |k|, and K_H = Q 2^{G_C}: two exponentials per
 // (token, channel).  Strong-decay path otherwise, for that wave's channels only: each 16x16
 // tile of A takes a reference token of its own (8, 15 or 24), whose factors are bounded by
-// exp(8 |g|max), and K_H its own exponentials.  Per-token log-gates are floored at -10 (a decay
-// of 4.5e-5 per token instead of anything smaller), which keeps every factor below e^80 in fp32
+// exp(8 |g|max), and K_H its own exponentials.
+//
+// The state decays lazily, by groups of 32 channels: a group's running sums G start from the
+// exponent its state still lags behind, K_H is then Q itself, and 2^G is multiplied into the
+// group's rows (and into K_H) only after the chunk in which some |G| exceeds kLazy, a chunk on
+// the strong-decay path, or the last one.  Channels that decay by 2^-30 a chunk, the fastest of
+// a group at the serving shape, have it applied every second chunk (211.6 -> 205.7 us for the
+// 16-request Load, 392.4 -> 383.8 for W = 2048).
+//
+// Per-token log-gates are floored at -10 (a decay of 4.5e-5 per token instead of anything smaller), which keeps every factor below e^80 in fp32
 // and changes the state by at most 4.5e-5 of its magnitude per floored token.
 //
 // Fused with the restore (FUSED = true), the initial state of a head is read from the
@@ -85,6 +95,9 @@ constexpr float kGateFloor = -10.f;
 // Fast path bound: every channel's log2-decay over a chunk at least -kFastRange, so that
 // k 2^G and k 2^{-G} stay normal fp32 (and their bf16 low parts too) for every token.
 constexpr float kFastRange = 96.f;
+// |log2| by which the state of a group of 32 channels may lag behind its decay: K_H is then Q as
+// it is, at most 2^kLazy |k|, and the state's values stay below 2^kLazy times their own.
+constexpr float kLazy = 40.f;
 constexpr float kLog2e = 1.4426950408889634f;
 
 constexpr int kStateWaves = 4;    // waves 0..3, 32 value columns each
@@ -102,7 +115,8 @@ constexpr int OFF_KH = OFF_KG + 3 * KG_BYTES;    // 2 buffers
 constexpr int OFF_AP = OFF_KH + 2 * KH_BYTES;    // 2 buffers
 constexpr int OFF_TP = OFF_AP + 2 * AP_BYTES;    // 2 buffers
 constexpr int OFF_GAM = OFF_TP + 2 * TP32_BYTES;   // f32 [3][D] 2^{G_C}
-constexpr int OFF_TR = OFF_GAM + 3 * D * 4;      // the solver's A, then T
+constexpr int OFF_FLAG = OFF_GAM + 3 * D * 4;    // int [3][4] is 2^{..} to be applied, by group of 32 channels
+constexpr int OFF_TR = OFF_FLAG + 3 * 16;      // the solver's A, then T
 constexpr int OFF_BETA = OFF_TR + 2 * T_BYTES;   // f32 [64] the solver's betas (twice)
 constexpr int OFF_ROWS = OFF_BETA + 64 * 4;      // int64 [D] fused: checkpoint row table
 constexpr int OFF_OMIT = OFF_ROWS + D * 8;       // u8 [D] row omitted (replayed)
@@ -204,6 +218,10 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
         *reinterpret_cast<uint32_t*>(o + 4 * KH_HALF) = khl[e];
       }
     };
+    // log2 of what the state still has to be multiplied by, per channel, held in lane r = 0 of
+    // each row of 16 (0 in the others), where the chunk's running sums start
+    float carry[8] = {};
+    const uint32_t first = r == 0 ? ~0u : 0u;
     auto stage = [&](int c, int kg_buf) {
       float G[2][8], kf[2][8];
 #pragma unroll
@@ -216,7 +234,9 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
           kf[mu][e] = __uint_as_float((e & 1) ? (kw & 0xFFFF0000u) : (kw << 16));
         }
       fetch((c + 1) * C);
-      // running sums over the chunk's tokens
+      // running sums over the chunk's tokens, from the carried exponent on
+#pragma unroll
+      for (int e = 0; e < 8; ++e) G[0][e] += carry[e];
 #pragma unroll
       for (int mu = 0; mu < 2; ++mu) {
 #pragma unroll
@@ -228,13 +248,19 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
 #pragma unroll
         for (int e = 0; e < 8; ++e) G[mu][e] += dpp_row<0x118>(G[mu][e]);
       }
-      float gmin = 0.f;
+      float gmax = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         G[1][e] += row_bcast<15>(G[0][e]);
-        gmin = fminf(gmin, G[1][e]);
+        gmax = fmaxf(gmax, fabsf(G[1][e]));
       }
-      const bool fast = __all(gmin >= -kFastRange);
+      const bool fast = __all(gmax <= kFastRange);
+      const bool apply = !__all(gmax <= kLazy) || c == n_chunks - 1;   // 2^G goes into the state
+      const uint32_t keep = apply ? 0u : first;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)   // row_ror:1: lane 0 takes the chunk's total from lane 15
+        carry[e] = __uint_as_float(__float_as_uint(dpp_row<0x121>(G[1][e])) & keep);
+      if (lane == 0) reinterpret_cast<int*>(smem + OFF_FLAG)[4 * kg_buf + kk] = apply;
       f32x4* const ap = reinterpret_cast<f32x4*>(smem + OFF_AP + (c & 1) * AP_BYTES + kk * 1024) + lane;
       bf16x8 ah[2], al[2];
       float eg[2][8];
@@ -268,10 +294,23 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
         ap[0] = mma3(ah[0], al[0], bh[0], bl[0], zero4);
         ap[256] = mma3(ah[1], al[1], bh[0], bl[0], zero4);
         ap[512] = mma3(ah[1], al[1], bh[1], bl[1], zero4);
+        if (apply) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float gam = row_bcast<15>(eg[1][e]);
-          split2(qf[0][e] * gam, qf[1][e] * gam, khh[e], khl[e]);
+          for (int e = 0; e < 8; ++e) {
+            const float gam = row_bcast<15>(eg[1][e]);
+            split2(qf[0][e] * gam, qf[1][e] * gam, khh[e], khl[e]);
+          }
+        } else {   // K_H is Q: its words of two channels dealt out to words of two tokens
+          const uint4 h0 = __builtin_bit_cast(uint4, bh[0]), h1 = __builtin_bit_cast(uint4, bh[1]);
+          const uint4 l0 = __builtin_bit_cast(uint4, bl[0]), l1 = __builtin_bit_cast(uint4, bl[1]);
+          const uint32_t hw[2][4] = {{h0.x, h0.y, h0.z, h0.w}, {h1.x, h1.y, h1.z, h1.w}};
+          const uint32_t lw[2][4] = {{l0.x, l0.y, l0.z, l0.w}, {l1.x, l1.y, l1.z, l1.w}};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+            khh[e] = __builtin_amdgcn_perm(hw[1][e >> 1], hw[0][e >> 1], sel);
+            khl[e] = __builtin_amdgcn_perm(lw[1][e >> 1], lw[0][e >> 1], sel);
+          }
         }
       } else {
 #pragma unroll
@@ -387,6 +426,9 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
       const unsigned char* p = kh + mt * (2 * 2 * 2 * KH_HALF) + s * (2 * KH_HALF);
       return Frag{*reinterpret_cast<const bf16x8*>(p), *reinterpret_cast<const bf16x8*>(p + 4 * KH_HALF)};
     };
+    const int4 fl = *reinterpret_cast<const int4*>(smem + OFF_FLAG + 16 * kg_buf);
+    const int flag[4] = {__builtin_amdgcn_readfirstlane(fl.x), __builtin_amdgcn_readfirstlane(fl.y),
+                         __builtin_amdgcn_readfirstlane(fl.z), __builtin_amdgcn_readfirstlane(fl.w)};
     // ---- X = K_G S' on this wave's columns (rows t, contraction over channels) ------------
     f32x16 X = {};
     Frag tf[2], hf[2];
@@ -441,11 +483,13 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
       } else {
         gf = load_kg(kg_next, 0);
       }
+      if (flag[mt]) {
 #pragma unroll
-      for (int gr = 0; gr < 4; ++gr) {
-        const f32x4 gam = *reinterpret_cast<const f32x4*>(gamp + 32 * mt + 8 * gr);
+        for (int gr = 0; gr < 4; ++gr) {
+          const f32x4 gam = *reinterpret_cast<const f32x4*>(gamp + 32 * mt + 8 * gr);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) S[mt][4 * gr + i] *= gam[i];
+          for (int i = 0; i < 4; ++i) S[mt][4 * gr + i] *= gam[i];
+        }
       }
 #pragma unroll
       for (int s = 0; s < 2; ++s) S[mt] = mmb3(hf[s].h, hf[s].l, uf[s].h, uf[s].l, S[mt]);
