@@ -566,8 +566,8 @@ def tp_stage1(D, sh, plan, T):
 
 def gdn_refresh_keys(torch, args, with_pack_restore=False, with_fused=False):
     """Refresh of the omitted v-heads of 8 requests over all 36 GDN layers at W = 1024
-    (each layer: the factor launch and the recurrence launch), per-layer durations by
-    batched HIP events.  Inputs are drawn on the device."""
+    (one launch per layer), per-layer durations by batched HIP events.  Inputs are drawn on
+    the device."""
     import paper_2608_30386_amd as D
     from workloads import WORKLOADS, log_lambda, refresh_inputs_device, states_device
 
@@ -600,7 +600,7 @@ def gdn_refresh_keys(torch, args, with_pack_restore=False, with_fused=False):
     bytes_ref = heads * per_head + key_heads * 2 * W * sh.dk
     out = {"workload": f"Qwen-GDN 36 layers, 16 qk / 32 v heads 128x128: refresh {n_req} requests "
                        f"x {heads // n_req // wl.n_layers} omitted heads per layer, W={W}",
-           "refresh_all_layers": {"tokens_per_s": n_req * W / (ms_all / 1e3), "launches": 2 * wl.n_layers,
+           "refresh_all_layers": {"tokens_per_s": n_req * W / (ms_all / 1e3), "launches": wl.n_layers,
                                   "per_layer_ms": ms_all / wl.n_layers, **_rate(ms_all, bytes_ref)},
            "bytes_per_layer": bytes_ref // wl.n_layers,
            "recurrence_TFLOPs": 5.0 * sh.dk * dv * W * heads / (ms_all / 1e3) / 1e12,
@@ -643,7 +643,7 @@ def bench_gdn(torch, args):
         "data": "synthetic", "config": {"workload": res["workload"]},
         "roofline": {"bound": "hbm", "achieved": r["GBps"], "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": r["hbm_frac"], "traffic": measured_traffic("qwen_gdn/refresh"),
-                     "kernel": "refresh (factor + recurrence per layer)",
+                     "kernel": "refresh (one launch per layer)",
                      "mfma_busy": measured_util("qwen_gdn/refresh", "mfma_busy"),
                      "valu_active": measured_util("qwen_gdn/refresh", "valu_active")},
         "kernels": res,
