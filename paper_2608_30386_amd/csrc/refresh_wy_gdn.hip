@@ -35,6 +35,9 @@
 // W = 1024: 80.3 -> 58.4; refresh of 3 requests, W = 517: 41.0 -> 27.9; 1 request of 4 heads,
 // W = 2048: 89.7 -> 84.0.
 //
+// Precision.  T = (I + A)^{-1} is formed in fp32 throughout, block (1, 0) on fp32 MFMA; what the
+// state products read of it is -T' with its rows scaled for the update, split into bf16 hi + lo.
+//
 // Register chaining, operand splitting and order, and the buffer-resource loads (tokens past
 // the window read as zeros: identity steps) are as in the channel-wise kernel; per-token
 // log-gates are floored at -10 in the same way.

@@ -94,4 +94,9 @@ __device__ inline f32x4 mma16(uint2 a, uint2 b, f32x4 c) {
                                                    __builtin_bit_cast(s16x4, b), c, 0, 0, 0);
 }
 
+// 16x16x4 fp32 MFMA: lane (q, r) holds A[r][q], B[q][r] and D[4q + i][r]
+__device__ inline f32x4 mma32(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
 }  // namespace dasc_wy

@@ -215,8 +215,24 @@ __device__ inline void solve_chunk(const float* a, const f32x4 a10, const float*
 #pragma unroll
   for (int i = 0; i < 4; ++i) t00[i] = tf[(4 * q + i) * ST + r];
   const f32x4 t11t = *reinterpret_cast<const f32x4*>(tf + (16 + r) * ST + 4 * q);
-  const f32x4 z = mulb(split4(a10), split4(t11t));
-  f32x4 t10 = mulb(split4(t00), split4(z)) * b0;   // -T10 Diag(beta)
+  f32x4 t10;
+  if (ROWF16) {
+    // GDN heads: both products in fp32 (16x16x4 MFMA, step i contracts the tokens 4q + i).  With
+    // correlated keys and betas near 1 the entries of T00 and T11 are large and cancel in T10:
+    // split bf16 products here cost 7.9e-5 of the state's norm instead of 1.7e-5 (keys of length
+    // 1.35 around one direction, beta = 1), 4.56e-6 instead of 4.54e-6 with independent keys.
+    // The fp32 MFMAs take up to 2% more time (1 request, W = 2048: 85.4 -> 87.5 us).
+    f32x4 z = {0.f, 0.f, 0.f, 0.f};
+    t10 = z;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) z = mma32(a10[i], t11t[i], z);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t10 = mma32(t00[i], z[i], t10);
+  } else {
+    const f32x4 z = mulb(split4(a10), split4(t11t));
+    t10 = mulb(split4(t00), split4(z));
+  }
+  t10 *= b0;   // -T10 Diag(beta)
   if (ROWF16) t10 *= rowf[16 + r];
   const Split4 o10 = split4(t10);
   unsigned char* const o1 = ROWF16 ? tp + 512 + (16 * q + r) * 16

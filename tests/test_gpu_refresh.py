@@ -457,3 +457,44 @@ def test_maximum_window(arch):
     assert pairs
     err = check(sh, pool, got, 0, inv, inp, pairs)
     announce(f"maximum window {arch}: max rel err {err:.2e}")
+
+
+# What the 128 x 128 kernels' arithmetic allows, as a share of a head's norm.  A split operand
+# (bf16 high and low part) is within 2^-18 of its value and a product of two drops the low parts'
+# product, 2^-18 again: 3 * 2^-18 per product.  Three products follow one another in a chunk.
+SPLIT_BOUND = 3 * 3 * 2.0 ** -18
+
+
+def norm_errors(sh, pool, got_pool, layer, inv, inp, pairs, slots):
+    """Per pair: 2-norm of the refreshed rows' error over the 2-norm of the rows."""
+    layer_in = np.stack([pool[s, layer] for s in slots])
+    H, dk = sh.n_heads, sh.dk
+    want, om = OR.refresh(layer_in, inv[layer * H * dk:(layer + 1) * H * dk], inp["k"], inp["v"],
+                          inp["g"], inp["beta"], sh.n_qk_heads, "restored", pairs=pairs)
+    errs = []
+    for (n, h), w in zip(pairs, want):
+        got = got_pool[slots[n], layer, h].astype(np.float64)
+        errs.append(np.linalg.norm((got - w)[om[h]]) / np.linalg.norm(w[om[h]]))
+    return np.array(errs)
+
+
+def test_gdn_correlated_keys():
+    # Keys of length 1.35 around one direction per key head, beta = 1, slow decays: the inverse
+    # of a chunk's I + A has large entries that cancel in its block (1, 0), so that block must
+    # not be formed from 16-bit operands.
+    n_req, H, Hqk, W = 3, 8, 4, 96
+    sh = D.Shape("gdn", 1, H, Hqk, 128, 128)
+    rng = np.random.default_rng(0)
+    inv = np.full(H * 128, -1, np.int32)
+    pool = (0.05 * rng.standard_normal((n_req, 1, H, 128, 128))).astype(np.float32)
+    inp = _inputs_128("gdn", n_req, H, Hqk, W, seed=1)
+    k = 0.3 * rng.standard_normal((n_req, Hqk, W, 128)) + rng.standard_normal((n_req, Hqk, 1, 128))
+    k *= 1.35 / np.linalg.norm(k, axis=-1, keepdims=True)
+    inp["k"] = bf16_bits_from_f32(k.astype(np.float32))
+    inp["beta"] = np.ones_like(inp["beta"])
+    inp["g"] = (-1e-3 * np.logaddexp(0, rng.standard_normal((n_req, H, W)))).astype(np.float32)
+    got = run_refresh(sh, pool, 0, inv, inp, W)
+    pairs = [(n, h) for n in range(n_req) for h in range(H)]
+    errs = norm_errors(sh, pool, got, 0, inv, inp, pairs, list(range(n_req)))
+    announce(f"gdn correlated keys: error of the norm mean {errs.mean():.2e} max {errs.max():.2e}")
+    assert errs.mean() <= SPLIT_BOUND
