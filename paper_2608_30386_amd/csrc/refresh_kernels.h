@@ -19,6 +19,10 @@ int refresh_impl(const dasc_shape* shape, int32_t layer, const int32_t* inv_row,
                  const void* workspace, size_t workspace_bytes, bool noalloc, int32_t kernel,
                  dasc_stream_t stream);
 
+// Heads of one launch of the chunkwise kernels: HIP counts a grid's threads in 32 bits, and
+// their blocks have up to 640, so longer lists of (request, head) pairs go in slices.
+constexpr unsigned kWyHeadsPerLaunch = 1u << 22;
+
 // Chunkwise WY-form kernel on bf16 MFMA; built for dk = dv = 128 only.
 bool refresh_wy_supported(int dk, int dv);
 void launch_refresh_wy(bool per_channel, int n_req, int H, int Hqk, int layer, int L,

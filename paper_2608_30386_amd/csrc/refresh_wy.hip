@@ -78,6 +78,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "ckpt_layout.h"
@@ -132,15 +133,16 @@ __device__ inline float row_bcast(float v) { return dpp_row<0x150 + L>(v); }
 
 template <bool PER_CHANNEL, bool FUSED>
 __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
-    int H, int Hqk, int layer, int L, const int32_t* __restrict__ inv_row,
+    int head0, int H, int Hqk, int layer, int L, const int32_t* __restrict__ inv_row,
     float* __restrict__ states, int64_t n_pool, const int32_t* __restrict__ slot,
     const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, const float* __restrict__ g,
     const float* __restrict__ beta, int W, int init_zero, CkptView ck) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[LDS_BYTES];
   unsigned char* const sOmit = smem + OFF_OMIT;
 
-  const int n = blockIdx.x / H;
-  const int h = blockIdx.x - n * H;
+  const int nh = head0 + int(blockIdx.x);
+  const int n = nh / H;
+  const int h = nh - n * H;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -511,18 +513,29 @@ namespace dasc {
 
 bool refresh_wy_supported(int dk, int dv) { return dk == D && dv == D; }
 
+template <bool FUSED>
+static void launch(bool per_channel, int n_req, int H, int Hqk, int layer, int L,
+                   const int32_t* inv_row, float* states, int64_t n_pool, const int32_t* slot,
+                   const uint16_t* k, const uint16_t* v, const float* g, const float* beta, int W,
+                   int init_zero, const CkptView& ck, hipStream_t st) {
+  const unsigned heads = unsigned(n_req) * unsigned(H);
+  for (unsigned h0 = 0; h0 < heads; h0 += kWyHeadsPerLaunch) {
+    const dim3 grid(std::min(heads - h0, kWyHeadsPerLaunch)), block(kThreads);
+    if (per_channel)
+      hipLaunchKernelGGL((refresh_wy_kernel<true, FUSED>), grid, block, 0, st, int(h0), H, Hqk, layer,
+                         L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, ck);
+    else
+      hipLaunchKernelGGL((refresh_wy_kernel<false, FUSED>), grid, block, 0, st, int(h0), H, Hqk, layer,
+                         L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, ck);
+  }
+}
+
 void launch_refresh_wy(bool per_channel, int n_req, int H, int Hqk, int layer, int L,
                        const int32_t* inv_row, float* states, int64_t n_pool, const int32_t* slot,
                        const uint16_t* k, const uint16_t* v, const float* g, const float* beta,
                        int W, int init_zero, hipStream_t st) {
-  const dim3 grid(unsigned(n_req) * unsigned(H)), block(kThreads);
-  const CkptView none{nullptr, 1, 1, 0, nullptr};
-  if (per_channel)
-    hipLaunchKernelGGL((refresh_wy_kernel<true, false>), grid, block, 0, st, H, Hqk, layer, L,
-                       inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, none);
-  else
-    hipLaunchKernelGGL((refresh_wy_kernel<false, false>), grid, block, 0, st, H, Hqk, layer, L,
-                       inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, none);
+  launch<false>(per_channel, n_req, H, Hqk, layer, L, inv_row, states, n_pool, slot, k, v, g, beta, W,
+                init_zero, CkptView{nullptr, 1, 1, 0, nullptr}, st);
 }
 
 void launch_restore_refresh_wy(bool per_channel, int n_req, int H, int Hqk, int layer, int L,
@@ -531,14 +544,8 @@ void launch_restore_refresh_wy(bool per_channel, int n_req, int H, int Hqk, int 
                                float* states, int64_t n_pool, const int32_t* slot,
                                const uint16_t* k, const uint16_t* v, const float* g,
                                const float* beta, int W, int init_zero, hipStream_t st) {
-  const dim3 grid(unsigned(n_req) * unsigned(H)), block(kThreads);
-  const CkptView ck{ckpt, n_ckpt_slots, slice_rows, n_rows, ck_slot};
-  if (per_channel)
-    hipLaunchKernelGGL((refresh_wy_kernel<true, true>), grid, block, 0, st, H, Hqk, layer, L,
-                       inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, ck);
-  else
-    hipLaunchKernelGGL((refresh_wy_kernel<false, true>), grid, block, 0, st, H, Hqk, layer, L,
-                       inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, ck);
+  launch<true>(per_channel, n_req, H, Hqk, layer, L, inv_row, states, n_pool, slot, k, v, g, beta, W,
+               init_zero, CkptView{ckpt, n_ckpt_slots, slice_rows, n_rows, ck_slot}, st);
 }
 
 }  // namespace dasc

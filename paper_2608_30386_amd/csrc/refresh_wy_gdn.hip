@@ -44,6 +44,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "ckpt_layout.h"
@@ -120,7 +121,7 @@ constexpr unsigned kSplitHeads = 128;
 // layer is written, as the channel-wise kernel's fused variant does.
 template <bool FUSED, int NS>
 __global__ __launch_bounds__(64 * (NS + 2)) void refresh_wy_gdn_kernel(
-    int H, int Hqk, int layer, int L, const int32_t* __restrict__ inv_row,
+    int head0, int H, int Hqk, int layer, int L, const int32_t* __restrict__ inv_row,
     float* __restrict__ states, int64_t n_pool, const int32_t* __restrict__ slot,
     const uint16_t* __restrict__ k, const uint16_t* __restrict__ v, const float* __restrict__ g,
     const float* __restrict__ beta, int W, int init_zero, dasc::CkptView ck) {
@@ -131,7 +132,7 @@ __global__ __launch_bounds__(64 * (NS + 2)) void refresh_wy_gdn_kernel(
 
   const int item = xcd_major(blockIdx.x, gridDim.x);
   const int part = item % kParts;
-  const int nh = item / kParts;
+  const int nh = head0 + item / kParts;
   const int n = nh / H;
   const int h = nh - n * H;
   const int tid = threadIdx.x;
@@ -417,11 +418,13 @@ static void launch(int n_req, int H, int Hqk, int layer, int L, const int32_t* i
                    hipStream_t st) {
   const unsigned heads = unsigned(n_req) * unsigned(H);
   if (heads <= kSplitHeads)
-    hipLaunchKernelGGL((refresh_wy_gdn_kernel<FUSED, 4>), dim3(2 * heads), dim3(64 * 6), 0, st, H, Hqk,
-                       layer, L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, ck);
+    hipLaunchKernelGGL((refresh_wy_gdn_kernel<FUSED, 4>), dim3(2 * heads), dim3(64 * 6), 0, st, 0, H,
+                       Hqk, layer, L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, ck);
   else
-    hipLaunchKernelGGL((refresh_wy_gdn_kernel<FUSED, 8>), dim3(heads), dim3(64 * 10), 0, st, H, Hqk,
-                       layer, L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, ck);
+    for (unsigned h0 = 0; h0 < heads; h0 += kWyHeadsPerLaunch)
+      hipLaunchKernelGGL((refresh_wy_gdn_kernel<FUSED, 8>), dim3(std::min(heads - h0, kWyHeadsPerLaunch)),
+                         dim3(64 * 10), 0, st, int(h0), H, Hqk, layer, L, inv_row, states, n_pool, slot,
+                         k, v, g, beta, W, init_zero, ck);
 }
 
 void launch_refresh_wy_gdn(int n_req, int H, int Hqk, int layer, int L, const int32_t* inv_row,

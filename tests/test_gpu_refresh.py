@@ -498,3 +498,56 @@ def test_gdn_correlated_keys():
     errs = norm_errors(sh, pool, got, 0, inv, inp, pairs, list(range(n_req)))
     announce(f"gdn correlated keys: error of the norm mean {errs.mean():.2e} max {errs.max():.2e}")
     assert errs.mean() <= SPLIT_BOUND
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("arch", ["kda", "gdn"])
+def test_more_heads_than_one_grid_holds(arch, fused):
+    # 7,536,640 heads: one block of 576 (KDA) or 640 (GDN) threads each would be more threads than
+    # the 2^32 a grid may have.  All requests but the first and the last have a slot outside the
+    # pool, which skips them; those two must come out as they do alone.
+    import torch
+
+    n_req, H, W = 1840, 4096, 1
+    sh = D.Shape(arch, 1, H, 1, 128, 128)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+
+    def rand(*shape):
+        return torch.randn(shape, generator=gen, device="cuda")
+
+    live = [0, n_req - 1]
+    inv = torch.arange(H * 128, dtype=torch.int32, device="cuda")
+    inv = torch.where((inv // 128) % 64 == 5, -1, inv)         # 64 of the 4096 heads refreshed
+    gs = (H, W, 128) if arch == "kda" else (H, W)
+    k = torch.zeros((n_req, 1, W, 128), dtype=torch.bfloat16, device="cuda")
+    v = torch.zeros((n_req, H, W, 128), dtype=torch.bfloat16, device="cuda")
+    g, beta = torch.zeros((n_req, *gs), device="cuda"), torch.zeros((n_req, H, W), device="cuda")
+    for i in live:
+        k[i] = (rand(1, W, 128) / 128 ** 0.5).to(torch.bfloat16)
+        v[i] = rand(H, W, 128).to(torch.bfloat16)
+        g[i], beta[i] = -rand(*gs).abs(), torch.sigmoid(rand(H, W))
+    pool = 0.05 * rand(2, 1, H, 128, 128)
+    ckpt = 0.05 * rand(2, H * 128, 128) if fused else None
+    ws_bytes = D.dasc_refresh_workspace_bytes(sh, n_req, W)
+
+    def call(states, slots, sel):
+        ids = torch.as_tensor(slots, dtype=torch.int32, device="cuda")
+        ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda") if ws_bytes else None
+        a = (k[sel], v[sel], g[sel], beta[sel], W)
+        announce(f"{'fused ' if fused else ''}refresh {sh} n_req={ids.numel()}")
+        if fused:
+            D.dasc_restore_refresh(sh, 0, ckpt, ids, inv, states, ids, *a, n_rows=H * 128, workspace=ws)
+        else:
+            D.dasc_refresh(sh, 0, inv, states, ids, *a, workspace=ws)
+        torch.cuda.synchronize()
+        return states
+
+    slots = [-1] * n_req
+    slots[0], slots[-1] = 0, 1
+    got = call(pool.clone(), slots, slice(None))
+    want = pool.clone()
+    for s, i in enumerate(live):
+        call(want, [s], slice(i, i + 1))
+    assert not torch.equal(want, pool)
+    assert torch.equal(got.view(torch.int32), want.view(torch.int32))
