@@ -121,7 +121,8 @@ constexpr int OFF_TR = OFF_FLAG + 3 * 16;      // the solver's A, then T
 constexpr int OFF_BETA = OFF_TR + 2 * T_BYTES;   // f32 [64] the solver's betas (twice)
 constexpr int OFF_ROWS = OFF_BETA + 64 * 4;      // int64 [D] fused: checkpoint row table
 constexpr int OFF_OMIT = OFF_ROWS + D * 8;       // u8 [D] row omitted (replayed)
-constexpr int LDS_BYTES = OFF_OMIT + D;
+constexpr int OFF_ANY = OFF_OMIT + D;            // int64 [2] fused: some_row of each half
+constexpr int LDS_BYTES = OFF_ANY + 16;
 static_assert(LDS_BYTES <= 160 * 1024, "one block per CU");
 
 // Packed checkpoint of the fused variant (unused when FUSED is false).
@@ -167,9 +168,14 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
   // (dasc::kOmitted for an omitted row, dasc::kNoRow for an index outside the packed rows,
   // which restores as +0.0).
   int64_t* sOff = reinterpret_cast<int64_t*>(smem + OFF_ROWS);
+  int64_t* sAny = reinterpret_cast<int64_t*>(smem + OFF_ANY);
   if (tid < D) {
     sOmit[tid] = inv < 0;
-    if (FUSED) sOff[tid] = dasc::ckpt_row_offset(inv, ck, cslot, D);
+    if (FUSED) {
+      const int64_t o = dasc::ckpt_row_offset(inv, ck, cslot, D);
+      sOff[tid] = o;
+      sAny[w] = some_row(o);
+    }
   }
   const bool any_omitted = __syncthreads_or(inv < 0);
   if (!FUSED && !any_omitted) return;
@@ -398,10 +404,11 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
   fetch_v(0);
   // S'[c][col] for c = 32 mt + (i % 4) + 8 (i / 4) + 4 hi
   f32x16 S[4] = {};
-  if (!init_zero) load_state<FUSED>(S, S_head, ck.ckpt, sOff, col, hi);
+  const int64_t any = FUSED ? std::max(sAny[0], sAny[1]) : 0;
+  if (!init_zero) load_state<FUSED>(S, S_head, ck.ckpt, sOff, any, col, hi);
   __syncthreads();
   // (kept rows are written while the first chunk is being solved)
-  if (FUSED) copy_kept_rows<64 * kStateWaves>(S_head, ck.ckpt, sOff, tid);
+  if (FUSED) copy_kept_rows<64 * kStateWaves>(S_head, ck.ckpt, sOff, any, tid);
   __syncthreads();
 
   struct Frag { bf16x8 h, l; };

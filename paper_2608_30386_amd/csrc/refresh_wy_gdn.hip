@@ -80,7 +80,8 @@ constexpr int OFF_G = OFF_B + 2 * C * 4;         // f32 [C]    G_t (factor wave)
 constexpr int OFF_T = OFF_G + C * 4;             // solver scratch
 constexpr int OFF_ROWS = OFF_T + T_BYTES;        // int64 [D] fused: checkpoint row table
 constexpr int OFF_OMIT = OFF_ROWS + D * 8;       // u8 [D] row omitted (replayed)
-constexpr int LDS_BYTES = OFF_OMIT + D;
+constexpr int OFF_ANY = OFF_OMIT + D;            // int64 [2] fused: some_row of each half
+constexpr int LDS_BYTES = OFF_ANY + 16;
 static_assert(OFF_ROWS % 16 == 0 && OFF_T % 16 == 0, "alignment");
 static_assert(LDS_BYTES <= 81920, "two blocks of six waves per CU");
 
@@ -148,9 +149,14 @@ __global__ __launch_bounds__(64 * (NS + 2)) void refresh_wy_gdn_kernel(
 
   // Fused: the head's checkpoint row table (float offsets, or dasc::kOmitted / dasc::kNoRow)
   int64_t* sOff = reinterpret_cast<int64_t*>(smem + OFF_ROWS);
+  int64_t* sAny = reinterpret_cast<int64_t*>(smem + OFF_ANY);
   if (tid < D) {
     sOmit[tid] = inv < 0;
-    if (FUSED) sOff[tid] = dasc::ckpt_row_offset(inv, ck, cslot, D);
+    if (FUSED) {
+      const int64_t o = dasc::ckpt_row_offset(inv, ck, cslot, D);
+      sOff[tid] = o;
+      sAny[w] = some_row(o);
+    }
   }
   const bool any_omitted = __syncthreads_or(inv < 0);
   if (!FUSED && !any_omitted) return;
@@ -286,10 +292,11 @@ __global__ __launch_bounds__(64 * (NS + 2)) void refresh_wy_gdn_kernel(
   };
   fetch_v(0);
   f32x4 S[8] = {};
-  if (!init_zero) load_state<FUSED>(S, S_head, ck.ckpt, sOff, col, q);
+  const int64_t any = FUSED ? std::max(sAny[0], sAny[1]) : 0;
+  if (!init_zero) load_state<FUSED>(S, S_head, ck.ckpt, sOff, any, col, q);
   __syncthreads();
   // (kept rows are written while the first chunk is being solved)
-  if (FUSED) copy_kept_rows<64 * 8>(S_head, ck.ckpt, sOff, 64 * NS * part + tid);
+  if (FUSED) copy_kept_rows<64 * 8>(S_head, ck.ckpt, sOff, any, 64 * NS * part + tid);
   __syncthreads();
 
   struct Frag { bf16x8 h, l; };

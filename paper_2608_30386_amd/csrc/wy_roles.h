@@ -36,14 +36,29 @@ template <> struct Tiles<f32x4> {
   __device__ static int row(int mt, int i, int q) { return 16 * mt + 4 * q + i; }
 };
 
+// Fused: some row that a 64-row half of the head reads from the checkpoint, by the wave whose lanes
+// hold the half's offsets (negative where it reads none).
+__device__ inline int64_t some_row(int64_t o) {
+  const uint64_t read = __ballot(o >= 0);
+  const int l = read ? __builtin_ctzll(read) : 0;
+  const uint32_t lo = __builtin_amdgcn_readlane(uint32_t(o), l);
+  const uint32_t hi = __builtin_amdgcn_readlane(uint32_t(uint64_t(o) >> 32), l);
+  return int64_t(uint64_t(hi) << 32 | lo);
+}
+
 // The initial state of this lane's column.  FUSED: from the packed checkpoint, off[c] being
-// row c's float offset (negative: the row restores as +0.0).  Such a row reads the head's own
-// pool row instead and drops it, so that no load waits on a branch.
+// row c's float offset (negative: the row restores as +0.0).  Such a row loads `any`, a row that
+// the head reads anyhow, and drops it, so that no load waits on a branch and none goes to memory
+// for nothing; a head that reads no row (any < 0) loads nothing.  Loading the head's own pool row
+// instead moved 25 MB more in the Load of 16 requests x 32 KDA heads; a branch per row moves as
+// little and takes longer (us, W = 16 and 64: pool row 27.5 and 35.2, branch 27.2 and 32.8, this
+// 25.7 and 32.6; 1 request, W = 16: 13.1, 13.7, 12.8).
 template <bool FUSED, typename TILE>
 __device__ inline void load_state(TILE (&S)[Tiles<TILE>::N], const float* S_head, const float* ckpt,
-                                  const int64_t* off, int col, int q) {
+                                  const int64_t* off, int64_t any, int col, int q) {
   using T = Tiles<TILE>;
   constexpr int R = T::REGS;
+  if (FUSED && any < 0) return;
 #pragma unroll
   for (int mt = 0; mt < T::N; ++mt) {
     float val[R];
@@ -56,7 +71,7 @@ __device__ inline void load_state(TILE (&S)[Tiles<TILE>::N], const float* S_head
       if (FUSED) {
         const int64_t o = off[c];
         ok[i] = o >= 0;
-        src = ok[i] ? ckpt + o : src;
+        src = ckpt + (ok[i] ? o : any);
       }
       val[i] = src[col];
     }
@@ -68,14 +83,19 @@ __device__ inline void load_state(TILE (&S)[Tiles<TILE>::N], const float* S_head
 // Fused: every row that is not replayed is final already; its checkpoint row (or +0.0) goes to
 // the pool, 16 bytes per thread and access, by THREADS threads.
 template <int THREADS>
-__device__ inline void copy_kept_rows(float* S_head, const float* ckpt, const int64_t* off, int tid) {
+__device__ inline void copy_kept_rows(float* S_head, const float* ckpt, const int64_t* off,
+                                      int64_t any, int tid) {
+  if (any < 0) {   // no row to read
+    for (int e = tid; e < kDim * kDim / 4; e += THREADS)
+      if (off[e >> 5] != dasc::kOmitted) reinterpret_cast<f32x4*>(S_head)[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    return;
+  }
 #pragma unroll 4
   for (int e = tid; e < kDim * kDim / 4; e += THREADS) {
-    const int c = e >> 5, v4 = e & 31;
-    const int64_t o = off[c];
-    const f32x4 val = reinterpret_cast<const f32x4*>(o >= 0 ? ckpt + o : S_head + int64_t(c) * kDim)[v4];
+    const int64_t o = off[e >> 5];
+    const f32x4 val = reinterpret_cast<const f32x4*>(ckpt + (o >= 0 ? o : any))[e & 31];
     if (o != dasc::kOmitted)
-      reinterpret_cast<f32x4*>(S_head + int64_t(c) * kDim)[v4] = o >= 0 ? val : f32x4{0.f, 0.f, 0.f, 0.f};
+      reinterpret_cast<f32x4*>(S_head)[e] = o >= 0 ? val : f32x4{0.f, 0.f, 0.f, 0.f};
   }
 }
 

@@ -228,3 +228,31 @@ def test_gdn_blocks_per_head(n_req):
     kept = got.reshape(n_req + 2, H, 128, 128)[dst][:, 2].view(np.uint32)
     assert np.array_equal(kept, restored.reshape(n_req, H, 128, 128)[:, 2])
     announce(f"gdn n_req={n_req}: fused bit-equal to unfused, max rel err {err:.2e}")
+
+
+@pytest.mark.parametrize("arch", ["kda", "gdn"])
+def test_heads_with_few_checkpoint_rows(arch):
+    # Rows that restore as zero load a row the head reads anyhow and drop it.  Heads with no such
+    # row (all omitted; the kept ones past the packed rows), with a single one at either end, and
+    # with omitted, kept and past-the-end rows mixed; the pool holds NaN before the call, so a
+    # value taken from it would show.
+    rng = np.random.default_rng(21)
+    n_req, W, R = 2, 40, 70
+    omit = [range(128), range(1, 128), range(127), range(3, 128), range(0, 128, 2), range(64),
+            range(64, 128)]
+    H = len(omit)
+    sh = D.Shape(arch, 1, H, H, 128, 128)
+    inv = rng.integers(0, R, size=(H, 128)).astype(np.int32)
+    for h, rows in enumerate(omit):
+        inv[h, list(rows)] = -1
+    inv[3, :3] = R + 5                        # no row to read: omitted and past the end only
+    inv[4, [1, 5, 127]] = R                   # just past the end, among kept rows
+    inv = inv.reshape(-1)
+    ck = (0.05 * rng.standard_normal((1, 3, R, 128))).astype(np.float32).view(np.uint32)
+    inp = _inputs_128(arch, n_req, H, H, W, seed=8)
+    pool = sentinel_pool(3, sh)
+    for init in ("restored", "zero"):
+        args = (sh, 0, ck, [2, 0], inv, pool, [1, 2], inp, W, R, 1, R, init)
+        got, ref = run_fused(*args).view(np.uint32), run_unfused(*args).view(np.uint32)
+        assert np.array_equal(got, ref)
+        assert np.isfinite(got.view(np.float32)[1:]).all()
