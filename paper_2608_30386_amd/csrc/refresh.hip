@@ -7,10 +7,10 @@
 // the single value v_t[j].  This kernel, for every head size the MFMA kernels are not built
 // for, holds a column in G = dk / 8 adjacent lanes, eight rows each, so that S~^T k_t is eight
 // products per lane and log2 G lane-shift additions (DPP), and a head of 64 x 64 runs on eight
-// waves.  Blocks of 256 threads take 2048 / dk columns of a (request, head); the columns of a
-// head that need more blocks repeat the staging of k and g.  k, exp(g), v and beta of the next
-// tile of tokens are loaded while a tile is worked on, and staged into the other of two LDS
-// buffers after it.
+// waves.  Blocks of 256 threads take 2048 / dk columns of a (request, head), smaller ones the
+// narrow heads of large calls (kNarrowHeads); the columns of a head that need more blocks repeat
+// the staging of k and g.  k, exp(g), v and beta of the next tile of tokens are loaded while a
+// tile is worked on, and staged into the other of two LDS buffers after it.
 //
 // What bounds it: the chain of one token (decay, products, lane additions, delta, update) at
 // about 250 cycles while the chip has no more than a wave or two per SIMD, which is any call of
@@ -19,8 +19,7 @@
 // leaves most SIMDs idle: 8 requests x 16 KDA heads of 64 x 64, W = 512: 619 us, now 58; 16 x 32
 // heads, W = 256: 324 -> 69; 8 x 16 heads of 16 x 16: 62 -> 27; 16 x 32 heads of 128 x 100: 641 ->
 // 225.  Two columns per lane (half the LDS reads per column) gain 5-9% from 512 heads of 64 or
-// more rows on and lose 40% below; 128 or 64 threads a block gain up to 10% for 16 rows and
-// lose up to 2.8x for 128.
+// more rows on and lose 40% below.
 //
 // Everything is fp32, the state within fp32 rounding of the per-token rule (3.7e-7 of its norm
 // after 512 tokens).  Only the omitted rows of the head (KDA) or the omitted heads (GDN) are
@@ -43,7 +42,14 @@ using dasc_wy::f32x2;
 using dasc_wy::f32x4;
 
 constexpr int kRows = 8;      // state rows per lane
-constexpr int NT = 256;       // threads per block
+// Heads of 16 or 32 rows whose columns need 64 or 128 lanes take blocks of that many threads from
+// this many heads on, where waves without a column would keep others off the chip; the other
+// calls take blocks of 256, of which fewer heads leave the chip idle and four waves stage a tile
+// sooner.  us, 256 threads -> 64 or 128: 64 requests x 32 heads of 16 x 16, W = 512: 213 -> 71 (a
+// thread per column: 177), of 16 x 4, W = 256: 108 -> 37 (83), of 32 x 32: 111 -> 75 (178); 512 heads
+// of 16 x 16, W = 256: 33.4 -> 29.8, of 32 x 32: 34.7 -> 32.7; 256 heads of 32 x 16: 29.2 -> 29.2, 128
+// heads, W = 512: 51.8 -> 53.4; 16 heads of 16 x 64: 48.5 -> 51.3.
+constexpr int64_t kNarrowHeads = 512;
 // Heads of one launch: the grid counts threads in 32 bits, so longer lists go in slices.
 constexpr int64_t kHeadsPerLaunch = int64_t(1) << 19;
 // Tokens staged per LDS tile.  32 measures 7-9% better than 16 for 16 or 32 rows (fewer
@@ -68,7 +74,7 @@ __device__ inline float group_sum(float x) {
   return x;
 }
 
-template <int DK, bool PER_CHANNEL>
+template <int DK, bool PER_CHANNEL, int NT>
 __global__ __launch_bounds__(NT) void refresh_column_kernel(
     int H, int Hqk, int dv, int layer, int L, const int32_t* __restrict__ inv_row,
     float* __restrict__ states, int64_t n_pool, const int32_t* __restrict__ slot,
@@ -232,22 +238,32 @@ __global__ __launch_bounds__(NT) void refresh_column_kernel(
   }
 }
 
-template <int DK>
-void launch_column(bool per_channel, int64_t heads, hipStream_t st, int H, int Hqk, int dv, int layer,
-                   int L, const int32_t* inv_row, float* states, int64_t n_pool,
-                   const int32_t* slot, const uint16_t* k, const uint16_t* v, const float* g,
-                   const float* beta, int W, int init_zero) {
+template <int DK, int NT>
+void launch_column_nt(bool per_channel, int64_t heads, hipStream_t st, int H, int Hqk, int dv, int layer,
+                      int L, const int32_t* inv_row, float* states, int64_t n_pool,
+                      const int32_t* slot, const uint16_t* k, const uint16_t* v, const float* g,
+                      const float* beta, int W, int init_zero) {
   constexpr int CB = NT / (DK / kRows);
   const int cbs = (dv + CB - 1) / CB;
   for (int64_t h0 = 0; h0 < heads; h0 += kHeadsPerLaunch) {
     const dim3 grid(unsigned(std::min(heads - h0, kHeadsPerLaunch) * cbs));
     if (per_channel)
-      hipLaunchKernelGGL((refresh_column_kernel<DK, true>), grid, dim3(NT), 0, st, H, Hqk, dv, layer,
+      hipLaunchKernelGGL((refresh_column_kernel<DK, true, NT>), grid, dim3(NT), 0, st, H, Hqk, dv, layer,
                          L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, int(h0), cbs);
     else
-      hipLaunchKernelGGL((refresh_column_kernel<DK, false>), grid, dim3(NT), 0, st, H, Hqk, dv, layer,
+      hipLaunchKernelGGL((refresh_column_kernel<DK, false, NT>), grid, dim3(NT), 0, st, H, Hqk, dv, layer,
                          L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, int(h0), cbs);
   }
+}
+
+template <int DK, class... A>
+void launch_column(bool per_channel, int64_t heads, hipStream_t st, int H, int Hqk, int dv, A... a) {
+  if (DK <= 32 && heads >= kNarrowHeads) {
+    const int lanes = dv * (DK / kRows);
+    if (lanes <= 64) return launch_column_nt<DK, 64>(per_channel, heads, st, H, Hqk, dv, a...);
+    if (lanes <= 128) return launch_column_nt<DK, 128>(per_channel, heads, st, H, Hqk, dv, a...);
+  }
+  launch_column_nt<DK, 256>(per_channel, heads, st, H, Hqk, dv, a...);
 }
 
 // Does this shape take the scalar-gate GDN kernel?

@@ -551,3 +551,36 @@ def test_more_heads_than_one_grid_holds(arch, fused):
         call(want, [s], slice(i, i + 1))
     assert not torch.equal(want, pool)
     assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+
+
+@pytest.mark.parametrize("arch,dk,dv", [
+    ("kda", 16, 4), ("gdn", 16, 32), ("kda", 16, 36), ("gdn", 16, 64), ("kda", 16, 68),
+    ("kda", 32, 16), ("gdn", 32, 20), ("kda", 32, 32), ("gdn", 32, 36),
+])
+def test_per_column_kernel_narrow_heads(arch, dk, dv):
+    # From 512 heads on, heads of 16 or 32 rows take blocks of 64 or 128 threads if these hold all
+    # their columns (dv * dk / 8 lanes).  A lane does the same whatever its block, so every request
+    # must come out bit for bit as in a call of its own (which takes 256 threads); the first and
+    # the last also against the oracle, within the rounding bound of the per-column kernel.
+    n_req, H, W = 128, 4, 35
+    sh = D.Shape(arch, 1, H, H, dk, dv)
+    rng = np.random.default_rng(dk + dv)
+    inv = rng.integers(-1, 1, size=(H, dk)) if arch == "kda" else np.full((H, dk), -1)
+    inv[1] = 0                                              # head 1 kept
+    inv = inv.astype(np.int32).reshape(-1)
+    pool = (0.05 * rng.standard_normal((n_req, 1, H, dk, dv))).astype(np.float32)
+    k = rng.standard_normal((n_req, H, W, dk)).astype(np.float32)
+    k /= np.linalg.norm(k, axis=-1, keepdims=True)
+    gshape = (n_req, H, W, dk) if arch == "kda" else (n_req, H, W)
+    inp = {
+        "k": bf16_bits_from_f32(k),
+        "v": bf16_bits_from_f32(rng.standard_normal((n_req, H, W, dv)).astype(np.float32)),
+        "g": (-0.3 * np.logaddexp(0, rng.standard_normal(gshape))).astype(np.float32),
+        "beta": (1 / (1 + np.exp(-rng.standard_normal((n_req, H, W))))).astype(np.float32),
+    }
+    got = run_refresh(sh, pool, 0, inv, inp, W)
+    for n in range(0, n_req, 9):
+        one = run_refresh(sh, pool[n:n + 1], 0, inv, {x: a[n:n + 1] for x, a in inp.items()}, W)
+        assert np.array_equal(one[0].view(np.uint32), got[n].view(np.uint32)), n
+    err = check(sh, pool, got, 0, inv, inp, [(n, h) for n in (0, n_req - 1) for h in range(H)])
+    assert err <= W * (dk + 4) * 2.0 ** -24, err
