@@ -22,7 +22,7 @@
 // chunk c, one factor wave that forms A and lays out the keys of chunk c + 2, one solver wave
 // that turns chunk c + 1's A into -T'; one barrier per chunk.  Two layouts: a block per head
 // with all eight state waves, or two blocks per head with four each (and a factor and a solver
-// wave of their own), chosen by kSplitHeads below.
+// wave of their own), chosen by kSplitHeads below.  ORDER: the refreshed heads first (kOrderHeads).
 //
 // What bounds it: a SIMD's waves for one chunk.  Two state waves alone on their SIMD take 2.9k
 // cycles; with the solver wave beside them (the factor and solver waves go first) 3.5k, and the
@@ -111,16 +111,46 @@ __device__ inline int xcd_major(int b, int n_blocks) {
   return (b & 7) * (n_blocks >> 3) + (b >> 3);
 }
 
-// Up to this many heads a launch takes two blocks per head: all of them run at once on the 256
-// CUs, each with the shorter chunk.  (Measured with 60 refreshed heads of 96: 27.9 us split, 33.4
-// whole.)  Beyond it blocks would share CUs or wait for one, and whole heads are better: 160 heads
-// of 256 58.4 us whole, 89.3 split; 240 of 384 92 against 108.
+// The r-th set bit of a mask that every lane holds.
+__device__ inline int nth_set(uint64_t mask, int lane, int r) {
+  const int below = __builtin_amdgcn_mbcnt_hi(uint32_t(mask >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(mask), 0));
+  return __builtin_ctzll(__ballot(((mask >> lane) & 1) && below == r));
+}
+
+// The (request, head) item of block b when the refreshed heads go first, in an XCD-major order of
+// their own, and the heads that the refresh leaves alone last.  inv: the layer's row map; a head's
+// first row stands for it here, which decides an order and nothing else.  For H <= 64.
+__device__ inline int refreshed_first(int b, int n_blocks, int H, const int32_t* inv, int lane) {
+  const uint64_t mask = __ballot(lane < H && inv[(lane < H ? lane : 0) * D] < 0);
+  const int cnt = __builtin_popcountll(mask), n_ref = n_blocks / H * cnt;
+  if (b < n_ref) {
+    const int x = b & 7, i = x * (n_ref >> 3) + min(x, n_ref & 7) + (b >> 3);
+    return i / cnt * H + nth_set(mask, lane, i % cnt);
+  }
+  const int i = b - n_ref, kept = H - cnt;
+  return i / kept * H + nth_set(~mask & (~uint64_t(0) >> (64 - H)), lane, i % kept);
+}
+
+// Up to kSplitHeads heads a launch takes two blocks per head: all of them run at once on the 256 CUs,
+// each with the shorter chunk.  Beyond it they may share CUs or wait for one: us, split and whole,
+// requests of 32 heads, 20 of them refreshed, W = 1024: 4 requests 49.9 and 59.0, 5 49.9 and 58.5, 6
+// 90.6 and 59.5, 8 91.4 and 59.9.  (The line counts heads, since the host does not see which are
+// refreshed; at 5 requests with as many kept it gives 9 us away.)
 constexpr unsigned kSplitHeads = 128;
+// From 257 heads, more than there are CUs, up to kOrderHeads a launch takes the refreshed heads first.
+// In list order the heads that exit at once leave CUs idle while refreshed ones queue for another
+// shader engine's, and the call takes two rounds even where the refreshed heads alone would fit
+// the chip: us, list order -> refreshed first, same heads, W = 1024: 9 requests 60.5 -> 62.8, 10 60.5
+// or 109.7 -> 62.5 (by the heads kept), 11 109.7 -> 63.4, 12 110.8 -> 63.2; W = 16: 12 17.0 -> 12.2.
+// Where they do not fit, finding the order only delays each block (13 to 16 requests: by 1% at W =
+// 1024, 4% at W = 256, 6% at W = 16), so the line stands at 1.5 heads per CU, which fits whenever a
+// third of the heads is kept.
+constexpr unsigned kOrderHeads = 384;
 
 // FUSED: the initial state comes from the packed checkpoint (kept rows from their packed
 // position, written back to the pool at once; omitted rows +0.0) and every row of the
 // layer is written, as the channel-wise kernel's fused variant does.
-template <bool FUSED, int NS>
+template <bool FUSED, int NS, bool ORDER>
 __global__ __launch_bounds__(64 * (NS + 2)) void refresh_wy_gdn_kernel(
     int head0, int H, int Hqk, int layer, int L, const int32_t* __restrict__ inv_row,
     float* __restrict__ states, int64_t n_pool, const int32_t* __restrict__ slot,
@@ -131,13 +161,14 @@ __global__ __launch_bounds__(64 * (NS + 2)) void refresh_wy_gdn_kernel(
   constexpr int kParts = 8 / NS;   // blocks per head
   unsigned char* const sOmit = smem + OFF_OMIT;
 
-  const int item = xcd_major(blockIdx.x, gridDim.x);
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int item = ORDER ? refreshed_first(blockIdx.x, gridDim.x, H, inv_row + int64_t(layer) * H * D, lane)
+                         : xcd_major(blockIdx.x, gridDim.x);
   const int part = item % kParts;
   const int nh = head0 + item / kParts;
   const int n = nh / H;
   const int h = nh - n * H;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane >> 4, r = lane & 15;
 
@@ -425,11 +456,14 @@ static void launch(int n_req, int H, int Hqk, int layer, int L, const int32_t* i
                    hipStream_t st) {
   const unsigned heads = unsigned(n_req) * unsigned(H);
   if (heads <= kSplitHeads)
-    hipLaunchKernelGGL((refresh_wy_gdn_kernel<FUSED, 4>), dim3(2 * heads), dim3(64 * 6), 0, st, 0, H,
+    hipLaunchKernelGGL((refresh_wy_gdn_kernel<FUSED, 4, false>), dim3(2 * heads), dim3(64 * 6), 0, st, 0, H,
                        Hqk, layer, L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, ck);
+  else if (heads > 256 && heads <= kOrderHeads && H <= 64)
+    hipLaunchKernelGGL((refresh_wy_gdn_kernel<FUSED, 8, true>), dim3(heads), dim3(64 * 10), 0, st, 0, H, Hqk,
+                       layer, L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, ck);
   else
     for (unsigned h0 = 0; h0 < heads; h0 += kWyHeadsPerLaunch)
-      hipLaunchKernelGGL((refresh_wy_gdn_kernel<FUSED, 8>), dim3(std::min(heads - h0, kWyHeadsPerLaunch)),
+      hipLaunchKernelGGL((refresh_wy_gdn_kernel<FUSED, 8, false>), dim3(std::min(heads - h0, kWyHeadsPerLaunch)),
                          dim3(64 * 10), 0, st, int(h0), H, Hqk, layer, L, inv_row, states, n_pool, slot,
                          k, v, g, beta, W, init_zero, ck);
 }

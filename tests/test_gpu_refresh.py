@@ -584,3 +584,41 @@ def test_per_column_kernel_narrow_heads(arch, dk, dv):
         assert np.array_equal(one[0].view(np.uint32), got[n].view(np.uint32)), n
     err = check(sh, pool, got, 0, inv, inp, [(n, h) for n in (0, n_req - 1) for h in range(H)])
     assert err <= W * (dk + 4) * 2.0 ** -24, err
+
+
+@pytest.mark.parametrize("H,n_req,keep", [
+    (32, 9, "some"), (32, 12, "some"), (64, 6, "some"), (64, 5, "none"), (5, 60, "some"),
+    (1, 300, "none"), (1, 300, "all"), (7, 54, "rows"), (33, 8, "rows"), (65, 5, "some"),
+])
+def test_gdn_refreshed_heads_first(H, n_req, keep):
+    # 257 to 384 heads of at most 64 a layer are dealt to the blocks with the refreshed ones first,
+    # a head's first row standing for it; every request must come out bit for bit as in a call of
+    # few heads.  keep: some heads, none, all, or single rows (also the first of a refreshed head,
+    # or all but the first of one that then counts as refreshed by it alone).
+    W = 40
+    sh = D.Shape("gdn", 1, H, 1, 128, 128)
+    assert 256 < n_req * H <= 384
+    rng = np.random.default_rng(H + n_req)
+    inv = np.full((H, 128), -1, np.int32)
+    if keep == "all":
+        inv[:] = 0
+    elif keep == "some":
+        inv[rng.permutation(H)[:max(1, 3 * H // 8)]] = 0
+    elif keep == "rows":
+        inv[0, 0] = 0
+        inv[1, 1:] = 0
+        inv[2:, :] = rng.integers(-1, 1, size=(H - 2, 128))
+        inv[3] = 0
+    inv = inv.reshape(-1)
+    pool = (0.05 * rng.standard_normal((n_req, 1, H, 128, 128))).astype(np.float32)
+    inp = _inputs_128("gdn", n_req, H, 1, W, seed=H)
+    got = run_refresh(sh, pool, 0, inv, inp, W)
+    step = max(1, 128 // H)
+    for n in range(0, n_req, step):
+        part = {x: a[n:n + step] for x, a in inp.items()}
+        few = run_refresh(sh, pool[n:n + step], 0, inv, part, W)
+        assert np.array_equal(few.view(np.uint32), got[n:n + step].view(np.uint32)), n
+    if keep != "all":
+        om = (inv < 0).reshape(H, 128)
+        heads = [h for h in range(H) if om[h].any()]
+        check(sh, pool, got, 0, inv, inp, [(n_req - 1, h) for h in (heads[0], heads[-1])])
