@@ -622,3 +622,72 @@ def test_gdn_refreshed_heads_first(H, n_req, keep):
         om = (inv < 0).reshape(H, 128)
         heads = [h for h in range(H) if om[h].any()]
         check(sh, pool, got, 0, inv, inp, [(n_req - 1, h) for h in (heads[0], heads[-1])])
+
+
+# log2 decays over each chunk of 32 tokens (the last one repeats), by group of 32 channels
+LAGS = {
+    "steady": ([5.0], [19.0], [39.0], [60.0]),          # applied at the end, every 3rd, 2nd, 1st chunk
+    "at the bound": ([13.3], [13.4], [20.0], [20.1]),   # 3 x 13.4 and 2 x 20.1 pass 40, the others not
+    "crossing": ([39.0, 60.0, 39.0], [200.0, 5.0], [5.0, 5.0, 200.0, 3.0], [30.0, 90.0, 30.0]),
+    "mixed": ([0.01], [39.9, 0.2], [10.0, 150.0, 10.0], [96.0, 1.0]),
+    "slow": ([0.1], [0.5], [1.0], [2.0]),               # carried to the end, most of the state kept
+}
+# the same by head for GDN, whose state may lag by 2^16
+GDN_LAGS = {
+    "steady": ([0.1], [1.0], [5.0], [60.0]),
+    "at the bound": ([5.3], [5.4], [8.0], [8.1]),
+    "mixed": ([15.9, 0.2], [4.0, 150.0, 4.0], [0.01], [300.0, 1.0, 15.5, 1.0]),
+}
+
+
+@pytest.mark.parametrize("W", [96, 201])
+@pytest.mark.parametrize("lags", LAGS)
+def test_kda_state_decay_carried_over_chunks(lags, W):
+    # The kernel multiplies the decay of 32 channels into the state only when it has lagged by 2^40:
+    # lags of several chunks, just below and above the bound, groups of one head that apply it in
+    # different chunks, a lag that takes a chunk past 2^96 onto the strong-decay path, and lags
+    # that follow or precede a chunk on it.  Each group of rows on its own, against what the split
+    # products allow, and the exponents: a running sum near 2^7 is within 2^-17 of its value, the
+    # decay then within 2^-17 ln 2.
+    n_req, H = 2, 3
+    sh = D.Shape("kda", 1, H, H, 128, 128)
+    rng = np.random.default_rng(W)
+    inv = np.full(H * 128, -1, np.int32)
+    pool = (0.05 * rng.standard_normal((n_req, 1, H, 128, 128))).astype(np.float32)
+    inp = _inputs_128("kda", n_req, H, H, W, seed=W + 2)
+    g = np.empty((W, 128))
+    for grp, per_chunk in enumerate(LAGS[lags]):
+        for t in range(W):
+            g[t, 32 * grp:32 * grp + 32] = -per_chunk[min(t // 32, len(per_chunk) - 1)] * math.log(2) / 32
+    inp["g"] = np.broadcast_to(g, (n_req, H, W, 128)).astype(np.float32)
+    pairs = [(n, h) for n in range(n_req) for h in range(H)]
+    for init in ("restored", "zero"):
+        got = run_refresh(sh, pool, 0, inv, inp, W, init)
+        want, _ = OR.refresh(pool[:, 0], inv, inp["k"], inp["v"], inp["g"], inp["beta"], H, init,
+                             pairs=pairs)
+        have = np.stack([got[n, 0, h] for n, h in pairs]).astype(np.float64)
+        d = (have - want).reshape(len(pairs), 4, -1)
+        err = np.linalg.norm(d, axis=-1) / np.linalg.norm(want.reshape(len(pairs), 4, -1), axis=-1)
+        announce(f"lags {lags} W={W} init={init}: error by group {[f'{e:.1e}' for e in err.max(axis=0)]}")
+        assert err.max() <= SPLIT_BOUND + 2.0 ** -17 * math.log(2)
+
+
+@pytest.mark.parametrize("n_req", [2, 33])
+@pytest.mark.parametrize("lags", GDN_LAGS)
+def test_gdn_state_decay_carried_over_chunks(lags, n_req):
+    # As above for GDN heads, four rates in the four heads of a request, with two blocks per head
+    # (8 heads) and with one (132).
+    H, W = 4, 201
+    sh = D.Shape("gdn", 1, H, 2, 128, 128)
+    rng = np.random.default_rng(n_req)
+    inv = np.full(H * 128, -1, np.int32)
+    pool = (0.05 * rng.standard_normal((n_req, 1, H, 128, 128))).astype(np.float32)
+    inp = _inputs_128("gdn", n_req, H, 2, W, seed=n_req + 2)
+    for h, per_chunk in enumerate(GDN_LAGS[lags]):
+        for t in range(W):
+            inp["g"][:, h, t] = -per_chunk[min(t // 32, len(per_chunk) - 1)] * math.log(2) / 32
+    pairs = [(n, h) for n in (0, n_req - 1) for h in range(H)]
+    got = run_refresh(sh, pool, 0, inv, inp, W)
+    errs = norm_errors(sh, pool, got, 0, inv, inp, pairs, list(range(n_req)))
+    announce(f"gdn lags {lags} n_req={n_req}: error {[f'{e:.1e}' for e in errs]}")
+    assert errs.max() <= SPLIT_BOUND + 2.0 ** -17 * math.log(2)
