@@ -276,6 +276,7 @@ size_t gdn_workspace_bytes(int n_req, int H, int W) {
   return size_t(n_req) * size_t(H) * size_t((int64_t(W) + 31) / 32) * size_t(4096);
 }
 // Largest request list the GDN path takes: heads times groups of four chunks within 32 bits.
+// Nothing in the kernels asks for it; it stays so that the same calls are taken and refused.
 bool gdn_size_ok(int n_req, int H, int W) {
   return int64_t(n_req) * H * (((int64_t(W) + 31) / 32 + 3) / 4) <= INT32_MAX;
 }
@@ -416,10 +417,10 @@ extern "C" int dasc_restore_refresh(const dasc_shape* shape, int32_t layer, cons
                                         W, init_mode == DASC_INIT_ZERO,
                                         reinterpret_cast<hipStream_t>(stream));
   } else
-    dasc::launch_restore_refresh_wy(shape->arch == DASC_ARCH_KDA, n_req, shape->n_heads,
-                                    shape->n_qk_heads, layer, shape->n_layers, ckpt, n_ckpt_slots,
-                                    src_slot, slice_rows, n_rows, inv_row, states, n_pool,
-                                    dst_slot, k, v, g, beta, W, init_mode == DASC_INIT_ZERO,
+    dasc::launch_restore_refresh_wy(n_req, shape->n_heads, shape->n_qk_heads, layer,
+                                    shape->n_layers, ckpt, n_ckpt_slots, src_slot, slice_rows,
+                                    n_rows, inv_row, states, n_pool, dst_slot, k, v, g, beta, W,
+                                    init_mode == DASC_INIT_ZERO,
                                     reinterpret_cast<hipStream_t>(stream));
   return dasc::launch_status();
 }

@@ -520,20 +520,16 @@ namespace dasc {
 
 bool refresh_wy_supported(int dk, int dv) { return dk == D && dv == D; }
 
-template <bool FUSED>
-static void launch(bool per_channel, int n_req, int H, int Hqk, int layer, int L,
-                   const int32_t* inv_row, float* states, int64_t n_pool, const int32_t* slot,
-                   const uint16_t* k, const uint16_t* v, const float* g, const float* beta, int W,
-                   int init_zero, const CkptView& ck, hipStream_t st) {
+template <bool PER_CHANNEL, bool FUSED>
+static void launch(int n_req, int H, int Hqk, int layer, int L, const int32_t* inv_row, float* states,
+                   int64_t n_pool, const int32_t* slot, const uint16_t* k, const uint16_t* v,
+                   const float* g, const float* beta, int W, int init_zero, const CkptView& ck,
+                   hipStream_t st) {
   const unsigned heads = unsigned(n_req) * unsigned(H);
   for (unsigned h0 = 0; h0 < heads; h0 += kWyHeadsPerLaunch) {
     const dim3 grid(std::min(heads - h0, kWyHeadsPerLaunch)), block(kThreads);
-    if (per_channel)
-      hipLaunchKernelGGL((refresh_wy_kernel<true, FUSED>), grid, block, 0, st, int(h0), H, Hqk, layer,
-                         L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, ck);
-    else
-      hipLaunchKernelGGL((refresh_wy_kernel<false, FUSED>), grid, block, 0, st, int(h0), H, Hqk, layer,
-                         L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, ck);
+    hipLaunchKernelGGL((refresh_wy_kernel<PER_CHANNEL, FUSED>), grid, block, 0, st, int(h0), H, Hqk, layer,
+                       L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero, ck);
   }
 }
 
@@ -541,18 +537,19 @@ void launch_refresh_wy(bool per_channel, int n_req, int H, int Hqk, int layer, i
                        const int32_t* inv_row, float* states, int64_t n_pool, const int32_t* slot,
                        const uint16_t* k, const uint16_t* v, const float* g, const float* beta,
                        int W, int init_zero, hipStream_t st) {
-  launch<false>(per_channel, n_req, H, Hqk, layer, L, inv_row, states, n_pool, slot, k, v, g, beta, W,
-                init_zero, CkptView{nullptr, 1, 1, 0, nullptr}, st);
+  const auto f = per_channel ? launch<true, false> : launch<false, false>;
+  f(n_req, H, Hqk, layer, L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero,
+    CkptView{nullptr, 1, 1, 0, nullptr}, st);
 }
 
-void launch_restore_refresh_wy(bool per_channel, int n_req, int H, int Hqk, int layer, int L,
-                               const float* ckpt, int64_t n_ckpt_slots, const int32_t* ck_slot,
+void launch_restore_refresh_wy(int n_req, int H, int Hqk, int layer, int L, const float* ckpt,
+                               int64_t n_ckpt_slots, const int32_t* ck_slot,
                                int64_t slice_rows, int64_t n_rows, const int32_t* inv_row,
                                float* states, int64_t n_pool, const int32_t* slot,
                                const uint16_t* k, const uint16_t* v, const float* g,
                                const float* beta, int W, int init_zero, hipStream_t st) {
-  launch<true>(per_channel, n_req, H, Hqk, layer, L, inv_row, states, n_pool, slot, k, v, g, beta, W,
-               init_zero, CkptView{ckpt, n_ckpt_slots, slice_rows, n_rows, ck_slot}, st);
+  launch<true, true>(n_req, H, Hqk, layer, L, inv_row, states, n_pool, slot, k, v, g, beta, W, init_zero,
+                     CkptView{ckpt, n_ckpt_slots, slice_rows, n_rows, ck_slot}, st);
 }
 
 }  // namespace dasc
