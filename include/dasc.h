@@ -309,7 +309,8 @@ int dasc_refresh_workspace_bytes(const dasc_shape *shape, int32_t n_req, int32_t
  * Precision.  The state is fp32 and bf16 inputs are widened exactly.  At dk = dv = 128 the
  * chunked WY form of Eq. 1 runs on bf16 matrix cores: every fp32 operand of a product is
  * split into bf16 high and low parts and the product is the sum of three bf16 products
- * (hi*hi + hi*lo + lo*hi) accumulated in fp32, about 16 significant bits per term; and
+ * (hi*hi + hi*lo + lo*hi; all four in part of the GDN kernel, which inverts a chunk's
+ * triangular system in fp32) accumulated in fp32, about 16 significant bits per term; and
  * each per-token log-gate is floored at -10 (a decay of at least 4.5e-5 per token, which
  * keeps the factorised decays finite; it changes the state by at most 4.5e-5 of its
  * magnitude per floored token).  Other shapes run a plain fp32 per-token recurrence with

@@ -17,8 +17,8 @@ extern "C" {
 #endif
 
 #define DASC_REFRESH_KERNEL_AUTO       0  /* the kernel dasc_refresh runs for this shape     */
-#define DASC_REFRESH_KERNEL_COLUMN     1  /* per-column fp32 kernel: one thread per value
-                                             column, plain per-token recurrence, no gate
+#define DASC_REFRESH_KERNEL_COLUMN     1  /* per-column fp32 kernel: a value column on dk / 8
+                                             lanes, plain per-token recurrence, no gate
                                              floor (dk in {16, 32, 64, 128}, dv <= 256)     */
 #define DASC_REFRESH_KERNEL_CHANNEL_WY 2  /* chunked WY kernel with channel-wise gates on
                                              bf16 MFMA, also for GDN heads (their scalar

@@ -16,9 +16,11 @@
 // about 250 cycles while the chip has no more than a wave or two per SIMD, which is any call of
 // up to a few hundred heads; vector issue (about 30 instructions per token and wave) beyond.  A
 // thread per column with its dk rows in registers instead does dk dependent FMAs a token and
-// leaves most SIMDs idle: 8 requests x 16 KDA heads of 64 x 64, W = 512: 619 us, now 58; 16 x 32
-// heads, W = 256: 324 -> 69; 8 x 16 heads of 16 x 16: 62 -> 27; 16 x 32 heads of 128 x 100: 641 ->
-// 225.  Two columns per lane (half the LDS reads per column) gain 5-9% from 512 heads of 64 or
+// leaves most SIMDs idle: 8 requests x 16 KDA heads of 64 x 64, W = 512: 619 us, now 58; at W = 256
+// 16 x 32 heads 325 -> 69, 8 x 16 heads of 16 x 16 63 -> 27, 16 x 32 heads of 128 x 100 643 -> 235 to
+// 260 (with the clock).  It is the faster one still for windows of one or two tokens of thousands
+// of heads of 64 or 128 rows (64 x 32 of 128 x 64: 54 and 69 at W = 1, 79 and 71 at W = 4), where the
+// prologue is all there is.  Two columns per lane (half the LDS reads per column) gain 5-9% from 512 heads of 64 or
 // more rows on and lose 40% below.
 //
 // Everything is fp32, the state within fp32 rounding of the per-token rule (3.7e-7 of its norm
@@ -53,8 +55,8 @@ constexpr int64_t kNarrowHeads = 512;
 // Heads of one launch: the grid counts threads in 32 bits, so longer lists go in slices.
 constexpr int64_t kHeadsPerLaunch = int64_t(1) << 19;
 // Tokens staged per LDS tile.  32 measures 7-9% better than 16 for 16 or 32 rows (fewer
-// barriers), but from 64 rows on its LDS (34 KB, 68 KB) costs resident blocks: 5-15% worse on
-// 512 heads.
+// barriers), but from 64 rows on its LDS (41 KB, 68 KB) costs resident blocks: 1-15% worse on
+// 512 heads (64 x 64 70 against 70.5 us, 128 x 100 257 against 296).
 constexpr int tile_tokens(int dk) { return dk <= 32 ? 32 : 16; }
 
 template <int CTRL>
@@ -91,7 +93,7 @@ __global__ __launch_bounds__(NT) void refresh_column_kernel(
   __shared__ float b_s[2][kTile];
 
   // the column blocks of a head are neighbours, so that they find its k and g in a cache
-  // (8 requests x 16 GDN heads of 128 x 256: 75 us, 98 with the columns as the grid's second
+  // (8 requests x 16 GDN heads of 128 x 256: 83 us, 104 with the columns as the grid's second
   // dimension)
   const int nh = head0 + int(blockIdx.x) / col_blocks;
   const int cb = int(blockIdx.x) % col_blocks;

@@ -31,15 +31,17 @@
 // priorities differ: the solver, which everything waits for, goes first, then the state waves.
 //
 // Measured (us; before: one 256-thread block per head, two per CU): fused Load of 16 requests x
-// 32 heads, W = 1024: 223.2 -> 205.7; the plain refresh, W = 2048: 426.3 -> 383.8; of 5
-// requests, W = 777: 126.8 -> 67.8; fused Load of 1 request, W = 128: 30.1 -> 19.5.  With all 256
-// CUs busy the clock falls from 2.45 to 2.1 GHz, which is why the batches gain less.
+// 32 heads, W = 1024: 225 -> 205; the plain refresh, W = 2048: 432 -> 387; of 5 requests, W = 777:
+// 127 -> 67; fused Load of 1 request, W = 128: 30.2 -> 19.3.  With all 256 CUs busy the clock falls from
+// 2.45 to 2.1 GHz, which is why the batches gain less.  One block per CU has nothing beside it
+// during its first loads and last stores: the plain refresh of 32 requests x 32 heads, W = 16, takes
+// 50 where two blocks per CU took 48.
 //
 // Precision.  The products run on bf16 MFMA with fp32 accumulation.  An fp32 operand x is
 // split into x_hi = bf16(x) and x_lo = bf16(x - x_hi); a product is formed as a_lo b_hi +
 // a_hi b_lo + a_hi b_hi, which keeps ~16 mantissa bits per term.  This is what lets an fp32
 // state survive thousands of tokens within 2e-3 while running at the bf16 matrix-core rate.
-// The diagonal blocks of T are fp32 throughout.
+// The diagonal blocks of T are fp32 throughout, block (1, 0) is formed by split products.
 //
 // Register-resident chaining.  The contraction index of an MFMA can be any bijection shared by
 // A and B, so accumulators are fed straight back as B operands: lane l of a 32x32x16 product
@@ -48,9 +50,9 @@
 // K_G S', V - K_G S' and U never leave registers.
 //
 // Decay factors.  exp(G_t - G_s) <= 1 for s <= t, but a factorised form needs
-// exp(G_t - G_ref) exp(G_ref - G_s).  Fast path: when each of a factor wave's 32 channels
-// decays by at most 2^96 over the chunk (a test per wave; realistic gates decay far less), the
-// reference is where G starts: A = Diag(beta) strictly-lower(K_G Q^T) with K_G = k 2^G (which
+// exp(G_t - G_ref) exp(G_ref - G_s).  Fast path: when none of a factor wave's 32 channels passes
+// 2^96 in the chunk, what the state lags behind included (see below; a test per wave, and
+// realistic gates decay far less), the reference is where G starts: A = Diag(beta) strictly-lower(K_G Q^T) with K_G = k 2^G (which
 // X needs anyway) and Q = k 2^{-G} <= 2^96 |k|, and K_H = Q 2^{G_C}: two exponentials per
 // (token, channel).  Strong-decay path otherwise, for that wave's channels only: each 16x16
 // tile of A takes a reference token of its own (8, 15 or 24), whose factors are bounded by
@@ -61,10 +63,11 @@
 // group's rows (and into K_H) only after the chunk in which some |G| exceeds kLazy, a chunk on
 // the strong-decay path, or the last one.  Channels that decay by 2^-30 a chunk, the fastest of
 // a group at the serving shape, have it applied every second chunk (211.6 -> 205.7 us for the
-// 16-request Load, 392.4 -> 383.8 for W = 2048).
+// 16-request Load, 392.4 -> 383.8 for W = 2048, when it came in).
 //
-// Per-token log-gates are floored at -10 (a decay of 4.5e-5 per token instead of anything smaller), which keeps every factor below e^80 in fp32
-// and changes the state by at most 4.5e-5 of its magnitude per floored token.
+// Per-token log-gates are floored at -10 (a decay of 4.5e-5 per token instead of anything
+// smaller), which keeps every factor below e^80 in fp32 and changes the state by at most 4.5e-5
+// of its magnitude per floored token.
 //
 // Fused with the restore (FUSED = true), the initial state of a head is read from the
 // packed checkpoint instead of the active state (kept rows from their packed position,
@@ -93,8 +96,9 @@ using namespace dasc_wy;
 constexpr int C = 32;       // tokens per chunk
 constexpr int D = kDim;     // dk = dv
 constexpr float kGateFloor = -10.f;
-// Fast path bound: every channel's log2-decay over a chunk at least -kFastRange, so that
-// k 2^G and k 2^{-G} stay normal fp32 (and their bf16 low parts too) for every token.
+// Fast path bound: |G| at the end of the chunk, the exponent carried into it included, at most
+// kFastRange, so that k 2^G and k 2^{-G} stay normal fp32 (and their bf16 low parts too) for
+// every token.
 constexpr float kFastRange = 96.f;
 // |log2| by which the state of a group of 32 channels may lag behind its decay: K_H is then Q as
 // it is, at most 2^kLazy |k|, and the state's values stay below 2^kLazy times their own.

@@ -15,8 +15,8 @@
 // The state decays lazily: it is held as S' = 2^c S^ with one exponent c per head, X is scaled
 // by 2^{c + G_t} and the rows of T' by 2^{-(c + G_t)}, and only when |c| would exceed kLazy, and
 // after the last chunk, is 2^c multiplied into the state (the rows of T' then take
-// 2^{G_C - G_t}, at most 1, as above).  Gates that decay by 2^-4 a chunk cost the 64
-// multiplications a chunk every fourth time.
+// 2^{G_C - G_t}, at most 1, as above).  Gates that decay by 2^-4 a chunk cost a lane's 32
+// multiplications every fifth chunk.
 //
 // Work split, as in the channel-wise kernel: eight state waves of 16 value columns each on
 // chunk c, one factor wave that forms A and lays out the keys of chunk c + 2, one solver wave
@@ -32,11 +32,17 @@
 //
 // Measured (us; before: a factor launch for all chunks, then a recurrence launch of two blocks
 // per head reading -T' back from memory): fused Load of one layer, 8 requests x 20 heads of 32,
-// W = 1024: 80.3 -> 58.4; refresh of 3 requests, W = 517: 41.0 -> 27.9; 1 request of 4 heads,
-// W = 2048: 89.7 -> 84.0.
+// W = 1024: 80.5 -> 58.6; refresh of 3 requests, W = 517: 41.1 -> 28.7; 1 request of 4 heads,
+// W = 2048: 107 -> 86.4.  Where more heads are refreshed than there are CUs the second round is
+// nearly empty, and a long window loses up to 7% against the two launches, whose half-head blocks
+// shared CUs (W = 1024: 13 requests 105 -> 113, 14 107 -> 113, 16 111 -> 114; W = 256: 16 44.5 -> 40; 24
+// requests, W = 1024: 188 -> 170).
 //
 // Precision.  T = (I + A)^{-1} is formed in fp32 throughout, block (1, 0) on fp32 MFMA; what the
 // state products read of it is -T' with its rows scaled for the update, split into bf16 hi + lo.
+// (The scale makes entries inexact that bf16 would hold, such as the diagonal's betas of 1 or
+// 0.5: 4.3e-6 of the state's norm instead of 3.7e-6 for beta = 0.5 and independent keys.  Scaling
+// U in fp32 instead avoids that and takes the 8-request refresh from 59.3 to 60.3 us.)
 //
 // Register chaining, operand splitting and order, and the buffer-resource loads (tokens past
 // the window read as zeros: identity steps) are as in the channel-wise kernel; per-token

@@ -223,7 +223,7 @@ def test_refresh_select_argument_errors():
     # the channel-wise chunked kernel exists for dk = dv = 128 only
     assert select(kda(dk=16, dv=16), E.DASC_REFRESH_KERNEL_CHANNEL_WY) == E.DASC_E_UNSUPPORTED
     assert select(kda(dk=64, dv=128), E.DASC_REFRESH_KERNEL_CHANNEL_WY) == E.DASC_E_UNSUPPORTED
-    # AUTO on GDN heads at 128 needs the factor workspace, like dasc_refresh
+    # AUTO on GDN heads at 128 asks for the workspace, like dasc_refresh
     gdn = Shape(_lib.DASC_ARCH_GDN, 1, 4, 2, 128, 128)
     assert select(gdn, E.DASC_REFRESH_KERNEL_AUTO, W=64, n_req=2) == E.DASC_E_WORKSPACE
     for name in ("inv", "states", "slot", "k", "v", "g", "beta"):
@@ -236,8 +236,8 @@ def test_refresh_select_argument_errors():
 
 def test_refresh_noalloc_argument_errors():
     # host-side checks of the entry point that allocates nothing: arguments are those of
-    # dasc_refresh, and a request whose factor records exceed the static scratch is
-    # refused before anything touches the device
+    # dasc_refresh, and a request whose workspace would exceed the limit that the interface
+    # states is refused before anything touches the device
     E = _lib
 
     def na(shape, n_req=1, W=8, ptrs=None):
@@ -284,7 +284,8 @@ def test_plan_padded_geometry_fields():
 
 
 def test_gdn_refresh_workspace():
-    # GDN heads at dk = dv = 128 keep one 4 KiB factor per (request, head, 32-token chunk)
+    # GDN heads at dk = dv = 128 are asked for 4 KiB per (request, head, 32-token chunk), which
+    # the interface states and the kernels leave untouched
     E = _lib
     gdn = Shape(_lib.DASC_ARCH_GDN, 2, 32, 16, 128, 128)
     need = C.c_size_t(0)

@@ -381,9 +381,8 @@ def test_gdn_scalar_gate_kernel_matches_channel_kernel():
 
 
 def test_gdn_workspace_reuse():
-    # the per-chunk factors live in a caller-owned workspace; one buffer reused by calls
-    # with different windows (the larger first, then a smaller one, which reads only
-    # what it wrote) gives the bits of a freshly drawn one
+    # the caller's workspace is asked for and left untouched: one buffer, full of another
+    # pattern and reused by calls with different windows, gives the bits of a freshly drawn one
     import torch
 
     L, H, Hqk, n_req = 1, 4, 2, 3
@@ -411,6 +410,7 @@ def test_gdn_workspace_reuse():
         assert np.array_equal(outs[0].view(np.uint32), outs[1].view(np.uint32))
         check(sh, pool, outs[0], 0, inv, inp, [(n, h) for n in range(n_req) for h in range(H)],
               slots=[2, 0, 1])
+    assert bool((ws == 0x7F).all())
 
 
 @pytest.mark.parametrize("arch", ["kda", "gdn"])
@@ -419,7 +419,7 @@ def test_maximum_window(arch):
     # (k = v = 0, g = 0, beta = 0: no decay, no update, exactly), so the result is the
     # oracle's replay of those 1024 tokens from the restored state.  The kernels still walk
     # the whole window: 65,536 chunks, input offsets up to 2^30 bytes, a 512 MiB GDN
-    # factor workspace.  GDN: two v-heads on one key head.
+    # workspace.  GDN: two v-heads on one key head.
     import torch
 
     W, tail = DASC_MAX_WINDOW, 1024

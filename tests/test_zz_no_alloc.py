@@ -1,9 +1,8 @@
-"""dasc_refresh_noalloc: the refresh with the library's static device scratch in place of
-a workspace, called through the C ABI, against dasc_refresh with a caller workspace on
-the same inputs.  The kernels are the same, so the results must agree bit for bit; two
-calls in a row (the second smaller) check that the shared scratch carries nothing from
-one call into the next.  The GDN shape is the one that uses the scratch (its per-chunk
-factor records); a KDA shape, which needs none, goes through the same entry."""
+"""dasc_refresh_noalloc: the refresh without a workspace argument, called through the C ABI,
+against dasc_refresh with a caller workspace on the same inputs.  The kernels are the same and
+use no device scratch, so the results must agree bit for bit, for a GDN shape (the one
+whose workspace the interface asks for) in two calls in a row, the second smaller, and for a
+KDA shape, which needs none."""
 
 import math
 
@@ -46,7 +45,7 @@ def test_noalloc_gdn_two_calls_second_smaller():
     sh = shape_of(wl)
     layer = 3
     rng = np.random.default_rng(3)
-    for n_req, W in ((8, 1024), (3, 200)):      # 32 MiB of factor records, then 2.5 MiB
+    for n_req, W in ((8, 1024), (3, 200)):      # workspaces of 32 MiB, then 2.6 MiB
         pool = (0.05 * rng.standard_normal((n_req + 1, wl.n_layers, 32, 128, 128))).astype(np.float32)
         pool.reshape(n_req + 1, -1, 128)[:, lib["inv_row"] < 0] = 0.0
         slots = list(range(1, n_req + 1))
