@@ -386,7 +386,7 @@ __global__ __launch_bounds__(kThreads) void refresh_wy_kernel(
           tr[(16 + 4 * q + i) * ST + r] = acc[2][i] * b1[i];
         }
         wave_lds_sync();
-        solve_chunk<false>(tr, a10, sB, b0, nullptr, tr + 32 * ST, smem + OFF_TP + (c & 1) * TP32_BYTES, q, r);
+        solve_chunk<false>(tr, a10, sB, b0, tr + 32 * ST, smem + OFF_TP + (c & 1) * TP32_BYTES, q, r);
       }
       __syncthreads();
     }

@@ -13,9 +13,9 @@
 // instead of three.
 //
 // The state decays lazily: it is held as S' = 2^c S^ with one exponent c per head, X is scaled
-// by 2^{c + G_t} and the rows of T' by 2^{-(c + G_t)}, and only when |c| would exceed kLazy, and
-// after the last chunk, is 2^c multiplied into the state (the rows of T' then take
-// 2^{G_C - G_t}, at most 1, as above).  Gates that decay by 2^-4 a chunk cost a lane's 32
+// by 2^{c + G_t} and U by 2^{-(c + G_t)}, and only when |c| would exceed kLazy, and after the last
+// chunk, is 2^c multiplied into the state (U then takes 2^{c + G_C - (c + G_t)}, at most 1, as
+// above).  Gates that decay by 2^-4 a chunk cost a lane's 32
 // multiplications every fifth chunk.
 //
 // Work split, as in the channel-wise kernel: eight state waves of 16 value columns each on
@@ -32,17 +32,17 @@
 //
 // Measured (us; before: a factor launch for all chunks, then a recurrence launch of two blocks
 // per head reading -T' back from memory): fused Load of one layer, 8 requests x 20 heads of 32,
-// W = 1024: 80.5 -> 58.6; refresh of 3 requests, W = 517: 41.1 -> 28.7; 1 request of 4 heads,
-// W = 2048: 107 -> 86.4.  Where more heads are refreshed than there are CUs the second round is
+// W = 1024: 80.5 -> 59.6; refresh of 3 requests, W = 517: 41.1 -> 28.2; 1 request of 4 heads,
+// W = 2048: 107 -> 84.  Where more heads are refreshed than there are CUs the second round is
 // nearly empty, and a long window loses up to 7% against the two launches, whose half-head blocks
 // shared CUs (W = 1024: 13 requests 105 -> 113, 14 107 -> 113, 16 111 -> 114; W = 256: 16 44.5 -> 40; 24
 // requests, W = 1024: 188 -> 170).
 //
-// Precision.  T = (I + A)^{-1} is formed in fp32 throughout, block (1, 0) on fp32 MFMA; what the
-// state products read of it is -T' with its rows scaled for the update, split into bf16 hi + lo.
-// (The scale makes entries inexact that bf16 would hold, such as the diagonal's betas of 1 or
-// 0.5: 4.3e-6 of the state's norm instead of 3.7e-6 for beta = 0.5 and independent keys.  Scaling
-// U in fp32 instead avoids that and takes the 8-request refresh from 59.3 to 60.3 us.)
+// Precision.  T = (I + A)^{-1} is formed in fp32 throughout, block (1, 0) on fp32 MFMA, and U's rows
+// are scaled in fp32; what the products read of T is -T', split into bf16 hi + lo.  Scaling the
+// rows of T' before they are split instead saves a state wave eight multiplications a chunk (1.5%
+// of the 8-request refresh) and loses the entries that bf16 holds exactly, such as a diagonal of
+// betas of 0.5: 4.3e-6 of the state's norm instead of 3.7e-6 with independent keys.
 //
 // Register chaining, operand splitting and order, and the buffer-resource loads (tokens past
 // the window read as zeros: identity steps) are as in the channel-wise kernel; per-token
@@ -80,8 +80,8 @@ constexpr int OFF_A = OFF_KT + 3 * KT_BYTES;     // 2 buffers
 constexpr int OFF_TP = OFF_A + 2 * A_BYTES;      // 2 buffers
 constexpr int OFF_EG = OFF_TP + 2 * TP16_BYTES;    // f32 [3][C] 2^{c + G_t}
 constexpr int OFF_GAM = OFF_EG + 3 * C * 4;      // f32 [4]    what the state is multiplied by
-constexpr int OFF_EU = OFF_GAM + 4 * 4;          // f32 [2][C] the scale of T's rows
-constexpr int OFF_B = OFF_EU + 2 * C * 4;        // f32 [2][C] beta
+constexpr int OFF_EU = OFF_GAM + 4 * 4;          // f32 [3][C] the scale of U's rows
+constexpr int OFF_B = OFF_EU + 3 * C * 4;        // f32 [2][C] beta
 constexpr int OFF_G = OFF_B + 2 * C * 4;         // f32 [C]    G_t (factor wave)
 constexpr int OFF_T = OFF_G + C * 4;             // solver scratch
 constexpr int OFF_ROWS = OFF_T + T_BYTES;        // int64 [D] fused: checkpoint row table
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(64 * (NS + 2)) void refresh_wy_gdn_kernel(
         sG[lane] = gl;
         sB[lane] = b_c;
         (reinterpret_cast<float*>(smem + OFF_EG) + buf * C)[lane] = ex2(gc);
-        (reinterpret_cast<float*>(smem + OFF_EU) + (c & 1) * C)[lane] = ex2((apply ? end : 0.f) - gc);
+        (reinterpret_cast<float*>(smem + OFF_EU) + buf * C)[lane] = ex2((apply ? end : 0.f) - gc);
       }
       if (lane == 0) reinterpret_cast<float*>(smem + OFF_GAM)[buf] = apply ? ex2(end) : 1.f;
       carry = apply ? 0.f : end;
@@ -308,7 +308,6 @@ __global__ __launch_bounds__(64 * (NS + 2)) void refresh_wy_gdn_kernel(
         const float* sB = reinterpret_cast<const float*>(smem + OFF_B) + par * C;
         solve_chunk<true>(sA, reinterpret_cast<const f32x4*>(sA + 32 * ST)[lane], sB,
                           *reinterpret_cast<const f32x4*>(sB + 4 * q),
-                          reinterpret_cast<const float*>(smem + OFF_EU) + par * C,
                           reinterpret_cast<float*>(smem + OFF_T), smem + OFF_TP + par * TP16_BYTES, q, r);
       }
       __syncthreads();
@@ -361,7 +360,7 @@ __global__ __launch_bounds__(64 * (NS + 2)) void refresh_wy_gdn_kernel(
     // ---- X = K S' on this wave's columns (rows t, contraction over channels) ---------------
     f32x4 X[2] = {};
     bf16x8 th[2], tl[2];
-    f32x4 eg[2];
+    f32x4 eg[2], eu[2];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
       KFrag kn;
@@ -376,8 +375,10 @@ __global__ __launch_bounds__(64 * (NS + 2)) void refresh_wy_gdn_kernel(
         th[1] = reinterpret_cast<const bf16x8*>(tp + 512)[lane];
         tl[1] = reinterpret_cast<const bf16x8*>(tp + 1536 + 512)[lane];
 #pragma unroll
-        for (int mu = 0; mu < 2; ++mu)
+        for (int mu = 0; mu < 2; ++mu) {
           eg[mu] = *reinterpret_cast<const f32x4*>(smem + OFF_EG + (buf * C + 16 * mu + 4 * q) * 4);
+          eu[mu] = *reinterpret_cast<const f32x4*>(smem + OFF_EU + (buf * C + 16 * mu + 4 * q) * 4);
+        }
       }
 #pragma unroll
       for (int mu = 0; mu < 2; ++mu) X[mu] = mma(kf.k[mu], sf.l, X[mu]);
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(64 * (NS + 2)) void refresh_wy_gdn_kernel(
       sf = sn;
     }
 
-    // ---- U = (-T')(Diag(2^{c + G}) X - V), its rows scaled for the update ------------------
+    // ---- U = (-T')(Diag(2^{c + G}) X - V), scaled for the update -----------------------------
     f32x4 U[2] = {};
     {
       float x[8];
@@ -405,7 +406,7 @@ __global__ __launch_bounds__(64 * (NS + 2)) void refresh_wy_gdn_kernel(
 #pragma unroll
       for (int mu = 0; mu < 2; ++mu) U[mu] = mma(th[mu], yl, U[mu]);
 #pragma unroll
-      for (int mu = 0; mu < 2; ++mu) U[mu] = mma(th[mu], yh, U[mu]);
+      for (int mu = 0; mu < 2; ++mu) U[mu] = mma(th[mu], yh, U[mu]) * eu[mu];
     }
     fetch_v((c + 1) * C);   // the next chunk's values (zeros past the window)
     bf16x8 hf[2] = {load_kt(0), load_kt(1)};

@@ -161,13 +161,12 @@ __device__ inline void clear_tp(unsigned char* tp, int lane) {
       *reinterpret_cast<uint4*>(tp + 2048 + 1024 * hl + lane * 16) = make_uint4(0, 0, 0, 0);
 }
 
-// -T' = -(I + A)^{-1} Diag(beta), split hi/lo for 32x32x16 products, or, with its rows scaled by
-// rowf[t], for 16x16x32 ones (ROWF16).  a: the diagonal blocks of A in LDS (row stride ST; only the entries
+// -T' = -(I + A)^{-1} Diag(beta), split hi/lo for 32x32x16 products or (TP16) for 16x16x32 ones.  a: the diagonal blocks of A in LDS (row stride ST; only the entries
 // below the diagonal are used); a10: block (1, 0) in the accumulator layout; b: the chunk's
 // betas in LDS, b0 those of tokens 4q .. 4q + 3; tf: T_BYTES of scratch.
-template <bool ROWF16>
+template <bool TP16>
 __device__ inline void solve_chunk(const float* a, const f32x4 a10, const float* b, const f32x4 b0,
-                                   const float* rowf, float* tf, unsigned char* tp, int q, int r) {
+                                   float* tf, unsigned char* tp, int q, int r) {
   // T = (I + A)^{-1} row by row from T (I + A) = I: lane r of diagonal block blk takes row r,
   // columns descending; once T[r][s] is known it is taken out of the columns before it
   // (T[r][c] -= T[r][s] A[s][c]), which need row s of A, the same for all lanes of the block.
@@ -208,14 +207,9 @@ __device__ inline void solve_chunk(const float* a, const f32x4 a10, const float*
     *reinterpret_cast<f32x4*>(tf + (16 * blk + r) * ST + 4 * h2) = ya;
     *reinterpret_cast<f32x4*>(tf + (16 * blk + r) * ST + 8 + 4 * h2) = yb;
   }
-  if (ROWF16) {
-    const float f = rowf[16 * blk + r];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] *= f;
-  }
   bf16x8 oh, ol;
   split8(o, oh, ol);
-  if (ROWF16) {   // token groups h2 and 2 + h2 of the row: lanes (h2, r) and (2 + h2, r)
+  if (TP16) {   // token groups h2 and 2 + h2 of the row: lanes (h2, r) and (2 + h2, r)
     unsigned char* const od = blk ? tp + 512 + 8 + (16 * h2 + r) * 16 : tp + (16 * h2 + r) * 8;
     const int step = blk ? 32 * 16 : 32 * 8;
     const uint4 hw = __builtin_bit_cast(uint4, oh), lw = __builtin_bit_cast(uint4, ol);
@@ -236,7 +230,7 @@ __device__ inline void solve_chunk(const float* a, const f32x4 a10, const float*
   for (int i = 0; i < 4; ++i) t00[i] = tf[(4 * q + i) * ST + r];
   const f32x4 t11t = *reinterpret_cast<const f32x4*>(tf + (16 + r) * ST + 4 * q);
   f32x4 t10;
-  if (ROWF16) {
+  if (TP16) {
     // GDN heads: both products in fp32 (16x16x4 MFMA, step i contracts the tokens 4q + i).  With
     // correlated keys and betas near 1 the entries of T00 and T11 are large and cancel in T10:
     // split bf16 products here cost 7.9e-5 of the state's norm instead of 1.7e-5 (keys of length
@@ -253,12 +247,11 @@ __device__ inline void solve_chunk(const float* a, const f32x4 a10, const float*
     t10 = mulb(split4(t00), split4(z));
   }
   t10 *= b0;   // -T10 Diag(beta)
-  if (ROWF16) t10 *= rowf[16 + r];
   const Split4 o10 = split4(t10);
-  unsigned char* const o1 = ROWF16 ? tp + 512 + (16 * q + r) * 16
+  unsigned char* const o1 = TP16 ? tp + 512 + (16 * q + r) * 16
                                    : tp + 256 + (r + 32 * (q & 1)) * 16 + (q >> 1) * 8;
   *reinterpret_cast<uint2*>(o1) = o10.h;
-  *reinterpret_cast<uint2*>(o1 + (ROWF16 ? 1536 : 1024)) = o10.l;
+  *reinterpret_cast<uint2*>(o1 + (TP16 ? 1536 : 1024)) = o10.l;
 }
 
 }  // namespace dasc_wy

@@ -459,9 +459,11 @@ def test_maximum_window(arch):
     announce(f"maximum window {arch}: max rel err {err:.2e}")
 
 
-# What the 128 x 128 kernels' arithmetic allows, as a share of a head's norm.  A split operand
-# (bf16 high and low part) is within 2^-18 of its value and a product of two drops the low parts'
-# product, 2^-18 again: 3 * 2^-18 per product.  Three products follow one another in a chunk.
+# What the 128 x 128 kernels' arithmetic allows, as a share of a head's norm.  Splitting an operand
+# into bf16 high and low parts (8 bits each) moves it by at most 2^-17, and a product of two drops
+# the low parts' product; over many entries the root mean square of each of these three is below
+# 2^-18 of its term (2.4e-6, 2.4e-6 and 2.6e-6).  Three products follow one another in a chunk.
+# All nine added up:
 SPLIT_BOUND = 3 * 3 * 2.0 ** -18
 
 
@@ -691,3 +693,28 @@ def test_gdn_state_decay_carried_over_chunks(lags, n_req):
     errs = norm_errors(sh, pool, got, 0, inv, inp, pairs, list(range(n_req)))
     announce(f"gdn lags {lags} n_req={n_req}: error {[f'{e:.1e}' for e in errs]}")
     assert errs.max() <= SPLIT_BOUND + 2.0 ** -17 * math.log(2)
+
+
+def test_gdn_update_scale_keeps_exact_betas():
+    # One chunk from a zero state with the unit vectors as keys: T is the identity, so row t of the
+    # state is 2^{..} beta_t v_t.  With betas that bf16 holds, T' and U are exact and the only
+    # rounding above fp32's is the split of the scaled U: the high part leaves at most half its last
+    # place, 2^-8 of the power of two below, the low part 2^-9 of that, so at most 2^-17 of each
+    # entry.  Exponents below 2 and the exponential add less than 2^-21.  Rounding T' too would
+    # double it.
+    n_req, H, W = 2, 4, 32
+    sh = D.Shape("gdn", 1, H, H, 128, 128)
+    rng = np.random.default_rng(4)
+    inv = np.full(H * 128, -1, np.int32)
+    pool = np.zeros((n_req, 1, H, 128, 128), np.float32)
+    inp = _inputs_128("gdn", n_req, H, H, W, seed=4)
+    inp["k"] = bf16_bits_from_f32(np.broadcast_to(np.eye(W, 128, dtype=np.float32), (n_req, H, W, 128)).copy())
+    inp["beta"] = rng.choice([0.25, 0.5, 1.0], size=(n_req, H, W)).astype(np.float32)
+    inp["g"] = (-0.04 * rng.random((n_req, H, W))).astype(np.float32)
+    got = run_refresh(sh, pool, 0, inv, inp, W, "zero")
+    pairs = [(n, h) for n in range(n_req) for h in range(H)]
+    want, _ = OR.refresh(pool[:, 0], inv, inp["k"], inp["v"], inp["g"], inp["beta"], H, "zero", pairs=pairs)
+    want = np.stack(want)[:, :W]
+    err = np.abs(got[:, 0].reshape(-1, 128, 128)[:, :W] - want) / np.abs(want)
+    announce(f"gdn unit keys, exact betas: largest relative error of an entry {err.max():.2e}")
+    assert err.max() <= 2.0 ** -17 + 2.0 ** -21
