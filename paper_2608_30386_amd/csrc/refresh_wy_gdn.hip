@@ -14,9 +14,8 @@
 //
 // The state decays lazily: it is held as S' = 2^c S^ with one exponent c per head, X is scaled
 // by 2^{c + G_t} and U by 2^{-(c + G_t)}, and only when |c| would exceed kLazy, and after the last
-// chunk, is 2^c multiplied into the state (U then takes 2^{c + G_C - (c + G_t)}, at most 1, as
-// above).  Gates that decay by 2^-4 a chunk cost a lane's 32
-// multiplications every fifth chunk.
+// chunk, is 2^c multiplied into the state (U then takes 2^{G_C - G_t}, at most 1, as above).
+// Gates that decay by 2^-4 a chunk cost a lane's 32 multiplications every fifth chunk.
 //
 // Work split, as in the channel-wise kernel: eight state waves of 16 value columns each on
 // chunk c, one factor wave that forms A and lays out the keys of chunk c + 2, one solver wave
@@ -32,16 +31,16 @@
 //
 // Measured (us; before: a factor launch for all chunks, then a recurrence launch of two blocks
 // per head reading -T' back from memory): fused Load of one layer, 8 requests x 20 heads of 32,
-// W = 1024: 80.5 -> 59.6; refresh of 3 requests, W = 517: 41.1 -> 28.2; 1 request of 4 heads,
-// W = 2048: 107 -> 84.  Where more heads are refreshed than there are CUs the second round is
-// nearly empty, and a long window loses up to 7% against the two launches, whose half-head blocks
-// shared CUs (W = 1024: 13 requests 105 -> 113, 14 107 -> 113, 16 111 -> 114; W = 256: 16 44.5 -> 40; 24
-// requests, W = 1024: 188 -> 170).
+// W = 1024: 80.5 -> 59.9; refresh of 3 requests, W = 517: 42.4 -> 28.0; 1 request of 4 heads,
+// W = 2048: 106 -> 84.  Where more heads are refreshed than there are CUs the second round is
+// nearly empty, and a long window loses up to 9% against the two launches, whose half-head blocks
+// shared CUs (W = 1024: 13 requests 105 -> 114, 14 107 -> 114, 16 111 -> 115; W = 256: 16 44.5 -> 41; 24
+// requests, W = 1024: 185 -> 171).
 //
 // Precision.  T = (I + A)^{-1} is formed in fp32 throughout, block (1, 0) on fp32 MFMA, and U's rows
 // are scaled in fp32; what the products read of T is -T', split into bf16 hi + lo.  Scaling the
-// rows of T' before they are split instead saves a state wave eight multiplications a chunk (1.5%
-// of the 8-request refresh) and loses the entries that bf16 holds exactly, such as a diagonal of
+// rows of T' before they are split instead saves a state wave eight multiplications a chunk (2% of
+// the 8-request refresh) and loses the entries that bf16 holds exactly, such as a diagonal of
 // betas of 0.5: 4.3e-6 of the state's norm instead of 3.7e-6 with independent keys.
 //
 // Register chaining, operand splitting and order, and the buffer-resource loads (tokens past
@@ -146,8 +145,8 @@ constexpr unsigned kSplitHeads = 128;
 // From 257 heads, more than there are CUs, up to kOrderHeads a launch takes the refreshed heads first.
 // In list order the heads that exit at once leave CUs idle while refreshed ones queue for another
 // shader engine's, and the call takes two rounds even where the refreshed heads alone would fit
-// the chip: us, list order -> refreshed first, same heads, W = 1024: 9 requests 60.5 -> 62.8, 10 60.5
-// or 109.7 -> 62.5 (by the heads kept), 11 109.7 -> 63.4, 12 110.8 -> 63.2; W = 16: 12 17.0 -> 12.2.
+// the chip: us, list order -> refreshed first, same heads, W = 1024: 9 requests 60 -> 62, 10 60 or
+// 110 -> 62 (by the heads kept), 11 110 -> 62, 12 111 -> 62; W = 16: 12 17.1 -> 12.2.
 // Where they do not fit, finding the order only delays each block (13 to 16 requests: by 1% at W =
 // 1024, 4% at W = 256, 6% at W = 16), so the line stands at 1.5 heads per CU, which fits whenever a
 // third of the heads is kept.

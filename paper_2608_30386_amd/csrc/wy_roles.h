@@ -235,7 +235,7 @@ __device__ inline void solve_chunk(const float* a, const f32x4 a10, const float*
     // correlated keys and betas near 1 the entries of T00 and T11 are large and cancel in T10:
     // split bf16 products here cost 7.9e-5 of the state's norm instead of 1.7e-5 (keys of length
     // 1.35 around one direction, beta = 1), 4.56e-6 instead of 4.54e-6 with independent keys.
-    // The fp32 MFMAs take up to 2% more time (1 request, W = 2048: 85.4 -> 87.5 us).
+    // The fp32 MFMAs take up to 1% more time (8-request refresh, W = 1024: 59.0 -> 59.3 us).
     f32x4 z = {0.f, 0.f, 0.f, 0.f};
     t10 = z;
 #pragma unroll
